@@ -26,12 +26,15 @@
 //   16 -> 1 layer keep ~16 significant bits of their weights by splitting
 //   them into a BF16 value and a BF16 remainder (for the last layer the two
 //   are rows 0 and 1 of one weight matrix, so the split costs nothing).
+// * Workgroups march through z by columns of the volume, so that a plane read
+//   once serves three planes of output.
 // * Weight gradients are reductions over all voxels: per-block FP64 partial
 //   sums, reduced in a fixed order (deterministic).
 #include <math.h>
 
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 
@@ -73,8 +76,9 @@ __device__ inline float read_scale(const double *norm2)
 
 // ------------------------------------------------------------- forward
 
-// Forward kernels work on output tiles of 16 x 4 x 4 voxels (one per
-// workgroup, on a 3-D grid: no index division).  The tile's input region
+// Activations past the marching kernels' reach take the 16 -> 16 layer by
+// output tiles of 16 x 4 x 4 voxels (one per workgroup, on a 3-D grid: no
+// index division).  The tile's input region
 // with its one-voxel halo (18 x 6 x 6) is staged in LDS once, zero outside
 // the volume, and every tap reads LDS instead of re-gathering from L2.
 // Wavefront w takes the four 16-voxel rows (y = 0..3, z = w) of the tile,
@@ -197,6 +201,25 @@ __device__ inline ConvOffsets conv_offsets(int vl, int lz, int g)
 // three independent MFMA instructions separate two that update the same
 // accumulator: an instruction then never reads as its accumulator input the
 // result of one still in flight.
+__device__ inline void conv_plane(const bf16x8 (&b32)[kRY], const bf16x4 (&b16)[kRY], int dz,
+                                  const bf16x8 (&w)[kTriples], const bf16x4 (&wt)[kTriples], f32x4 (&acc)[kTY])
+{
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy) {
+#pragma unroll
+        for (int y = 0; y < kTY; ++y)
+            acc[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[3 * dz + dy], b32[y + dy], acc[y], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);  // keep the four-row interleave as written
+    }
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy) {
+#pragma unroll
+        for (int y = 0; y < kTY; ++y)
+            acc[y] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wt[3 * dz + dy], b16[y + dy], acc[y], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 __device__ inline void conv_rows(const char *rbytes, const ConvOffsets &o, const bf16x8 (&w)[kTriples],
                                  const bf16x4 (&wt)[kTriples], f32x4 (&acc)[kTY])
 {
@@ -210,20 +233,7 @@ __device__ inline void conv_rows(const char *rbytes, const ConvOffsets &o, const
             b32[yi] = *reinterpret_cast<const bf16x8 *>(rbytes + o.k32 + row);
             b16[yi] = *reinterpret_cast<const bf16x4 *>(rbytes + o.k16 + row);
         }
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-#pragma unroll
-            for (int y = 0; y < kTY; ++y)
-                acc[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[3 * dz + dy], b32[y + dy], acc[y], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);  // keep the four-row interleave as written
-        }
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-#pragma unroll
-            for (int y = 0; y < kTY; ++y)
-                acc[y] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wt[3 * dz + dy], b16[y + dy], acc[y], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        conv_plane(b32, b16, dz, w, wt, acc);
     }
 }
 
@@ -235,73 +245,6 @@ __device__ inline void load_conv_frags(const bf16x8 *__restrict__ frag, int lane
         w[q] = frag[q * 64 + lane];
         const bf16x8 t = frag[(kTriples + q) * 64 + lane];
         wt[q] = __builtin_shufflevector(t, t, 0, 1, 2, 3);
-    }
-}
-
-// layer 1: a1[v][c] = relu(b1[c] + sum_t w1[c][t] x[v + t - 1] / s), on
-// MFMA with the taps as the contraction index (k = tap, 27-31 with zero
-// weight).  Weights and inputs are each split into a BF16 value and a BF16
-// remainder, and the three products that matter (hi hi, hi lo, lo hi) keep
-// ~16 significant bits: three v_mfma_f32_16x16x32_bf16 per 16-voxel row.
-__global__ __launch_bounds__(kThreads) void k_conv1(const bf16x8 *__restrict__ frag1,
-                                                    const float *__restrict__ P,
-                                                    const float *__restrict__ x, Vol d,
-                                                    const double *__restrict__ norm2,
-                                                    uint16_t *__restrict__ a1,
-                                                    const int *__restrict__ skip)
-{
-    __shared__ float xs[kRegion];
-    if (skip && *skip) return;
-    const float s = read_scale(norm2);
-    const float inv = s > 0.0f ? 1.0f / s : 0.0f;
-    const int x0 = blockIdx.x * kTX, y0 = blockIdx.y * kTY, z0 = blockIdx.z * kTZ;
-    for (int e = threadIdx.x; e < kRegion; e += kThreads) {
-        const int ex = e % kRX, ey = (e / kRX) % kRY, ez = e / (kRX * kRY);
-        const int gx = x0 + ex - 1, gy = y0 + ey - 1, gz = z0 + ez - 1;
-        float v = 0.0f;
-        if (gx >= 0 && gx < d.nx && gy >= 0 && gy < d.ny && gz >= 0 && gz < d.nz)
-            v = x[((int64_t)gz * d.ny + gy) * d.nx + gx] * inv;
-        xs[e] = v;
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bf16x8 wh = frag1[lane], wl = frag1[64 + lane];  // BF16 weights, remainders
-    const int vl = lane % 16, g = lane / 16, cg = 4 * g;
-    // taps 8g..8g+7 of this lane; taps past 26 read tap 26 (zero weight)
-    int off[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) off[e] = region_index(vl, 0, wave, min(8 * g + e, kTaps - 1));
-    float b[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) b[r] = P[OB1 + cg + r];
-    __syncthreads();
-    f32x4 acc[kTY];
-#pragma unroll
-    for (int y = 0; y < kTY; ++y) {
-        // inputs split the same way: x = bf16(x) + bf16(x - bf16(x)) (+ tiny)
-        bf16x8 xh, xl;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float v = xs[off[e] + y * kRX];
-            const uint16_t h = f2bf(v);
-            xh[e] = (short)h;
-            xl[e] = (short)f2bf(v - bf2f(h));
-        }
-        acc[y] = f32x4{0.f, 0.f, 0.f, 0.f};
-        acc[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh, xh, acc[y], 0, 0, 0);
-        acc[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh, xl, acc[y], 0, 0, 0);
-        acc[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wl, xh, acc[y], 0, 0, 0);
-    }
-    const int xo = x0 + vl, zo = z0 + wave;
-#pragma unroll
-    for (int y = 0; y < kTY; ++y) {
-        const int yo = y0 + y;
-        if (xo < d.nx && yo < d.ny && zo < d.nz) {
-            const int64_t vo = ((int64_t)zo * d.ny + yo) * d.nx + xo;
-            bf16x4 o;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = (short)f2bf(fmaxf(acc[y][r] + b[r], 0.0f));
-            *reinterpret_cast<bf16x4 *>(a1 + vo * kC + cg) = o;
-        }
     }
 }
 
@@ -428,139 +371,291 @@ __global__ __launch_bounds__(kThreads) void k_conv3(const bf16x8 *__restrict__ f
     conv3_store(acc, s, b3, d, x0, y0, z0, map_mask, out);
 }
 
-// ---- persistent forward kernels (inference): each workgroup takes tiles
-// t, t + G, t + 2G, ... (G workgroups) and, while it computes one, the
-// region of its next tile arrives in the other of two LDS buffers through
-// direct-to-LDS buffer loads (no registers, no staging stores), so the
-// staging latency hides behind the MFMA work instead of adding to it.
-// Each tile's arithmetic is that of k_conv16 / k_conv3, bit for bit.
-constexpr int kChunks = (2 * kRegion + 63) / 64;  // 64-slot wave loads per region
-constexpr int kSlots = kChunks * 64;              // region buffer with its padding
+// ---- marching kernels: a workgroup owns a column of the volume over x and y
+// and walks z plane by plane, so that a plane is read for the three planes of
+// output it feeds while it is in LDS (or registers) instead of once per tile
+// above and below: 1.27 reads per input voxel of a 16 x 16 column (plus two
+// planes per workgroup) against 2.53 for 16 x 4 x 4 tiles.
 
-// Issues the loads of the region of the tile at (x0, y0, z0) into buf: slot
-// s of plane h = s / kRegion holds channels 8h..8h+7 of region voxel
-// s % kRegion; voxels outside the volume and the padding get offsets past
-// the buffer's range, which the hardware reads as zeros.  Lane l of a wave
-// load writes slot 64 c + l.  rs spans the [voxel][16] BF16 activation.
-__device__ inline void stage_channels_lds(__amdgpu_buffer_rsrc_t rs, const Vol &d, int x0, int y0, int z0,
-                                          uint4 *buf)
+// Workgroup b of a marching launch: its column (cx, cy) and planes [z0, z1).
+struct March {
+    int32_t ncx, ncy, cz;  // columns along x and y, planes per workgroup
+};
+
+__device__ inline bool march_place(const March &m, const Vol &d, int &cx, int &cy, int &z0, int &z1)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int c = wave; c < kChunks; c += kThreads / 64) {
-        const int sl = c * 64 + lane;
-        uint32_t off = 0xFFFFFFF0u;
-        if (sl < 2 * kRegion) {
-            const int h = sl >= kRegion ? 1 : 0, rv = sl - h * kRegion;
-            const int ex = rv % kRX, ey = (rv / kRX) % kRY, ez = rv / (kRX * kRY);
-            const int gx = x0 + ex - 1, gy = y0 + ey - 1, gz = z0 + ez - 1;
-            if (gx >= 0 && gx < d.nx && gy >= 0 && gy < d.ny && gz >= 0 && gz < d.nz)
-                off = (uint32_t)((((int64_t)gz * d.ny + gy) * d.nx + gx) * (kC * 2) + h * 16);
-        }
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(buf + c * 64), 16,
-                                                 (int)off, 0, 0, 0);
-    }
+    const int b = (int)xcd_remap(blockIdx.x, gridDim.x);
+    cx = b % m.ncx;
+    const int r = b / m.ncx;
+    cy = r % m.ncy;
+    z0 = (r / m.ncy) * m.cz;
+    z1 = min(z0 + m.cz, d.nz);
+    return z0 < z1;
 }
 
-// Largest activation the persistent kernels address through one buffer
+constexpr int kZX = 16, kZY = 16, kZR = kZX + 2;  // a column's outputs; rows and columns of its input plane
+constexpr int kZPlane = kZR * (kZY + 2);          // input voxels of a plane
+constexpr int kZLoads = (2 * kZPlane + kThreads - 1) / kThreads;
+static_assert(kZY == 4 * (kThreads / 64), "four rows per wavefront");
+
+// Largest activation the marching 16 -> 16 kernel addresses through one buffer
 // resource (offsets below the out-of-range marker).
-constexpr int64_t kMaxPipelinedVoxels = ((int64_t)1 << 27) - 1;
+constexpr int64_t kMaxMarchVoxels = ((int64_t)1 << 27) - 1;
 
-// The tile loop of a persistent forward kernel: tile(region, x0, y0, z0)
-// computes and stores one tile from a published region.  The two buffers
-// alternate at compile time (two tiles per round).
-template <class Tile>
-__device__ inline void pipelined_tiles(const uint16_t *__restrict__ in, const Vol &d, uint4 *buf0, uint4 *buf1,
-                                       Tile &&tile)
-{
-    const int ntx = (d.nx + kTX - 1) / kTX, nty = (d.ny + kTY - 1) / kTY, ntz = (d.nz + kTZ - 1) / kTZ;
-    const int T = ntx * nty * ntz;
-    const auto rs = make_rsrc(in, (uint32_t)(d.n * kC * 2));
-    auto origin = [&](int t, int &x0, int &y0, int &z0) {
-        x0 = (t % ntx) * kTX;
-        const int r = t / ntx;
-        y0 = (r % nty) * kTY;
-        z0 = (r / nty) * kTZ;
-    };
-    int t = blockIdx.x, x0, y0, z0;
-    if (t >= T) return;
-    origin(t, x0, y0, z0);
-    stage_channels_lds(rs, d, x0, y0, z0, buf0);
-    // one step: publish cur (its loads done, every wave past the previous
-    // tile, so next is free), prefetch the next tile into next, compute t
-    auto step = [&](uint4 *cur, uint4 *next) -> bool {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        const int tn = t + (int)gridDim.x;
-        int nx0 = 0, ny0 = 0, nz0 = 0;
-        if (tn < T) {
-            origin(tn, nx0, ny0, nz0);
-            stage_channels_lds(rs, d, nx0, ny0, nz0, next);
-        }
-        tile(cur, x0, y0, z0);
-        if (tn >= T) return false;
-        t = tn;
-        x0 = nx0;
-        y0 = ny0;
-        z0 = nz0;
-        return true;
-    };
-    while (step(buf0, buf1) && step(buf1, buf0)) {
-    }
-}
-
-// Persistent 16 -> 16 layer with ReLU (the inference forward's layer 2).
-__global__ __launch_bounds__(kThreads) void k_conv16p(const uint16_t *__restrict__ in,
+// A layer of 16 input channels by 16 x 16 columns.  Four input planes live in LDS (two
+// 16-byte halves per voxel, as in stage_channels): three feed the current
+// output plane while the fourth arrives by direct-to-LDS buffer loads, whose
+// out-of-range offsets (voxels outside the volume) read zeros.  Each wavefront
+// computes four rows per plane with conv_rows' arithmetic and order, and
+// stores them after the next plane's barrier, so that the wait for the
+// arriving plane never waits for a fresh store.
+// 128^3: layer 2 35.9 us (40.7 with persistent 16 x 4 x 4 tiles, 2.53 reads per
+// input voxel), its data gradient 39.5 (61.3), layer 3 32.4 (37.1).  The MFMA
+// pipe is busy for 15 us of each and LDS reads take as long, in phases that
+// the three workgroups of a CU overlap in part.  Prefetching the next plane's
+// operands into registers cost the third workgroup and won nothing.
+// kMode: what the products become.
+//   kForward: out = ReLU(bias + conv);
+//   kMasked: out = conv where mask > 0, else 0 (the data gradient through the
+//     ReLU below);
+//   kLast: the 16 -> 1 layer, whose weights are rows 0 (BF16 value) and 1 (BF16
+//     remainder) of the matrix: zout = s (bias + row 0 + row 1), s =
+//     sqrt(*norm2) (or 1), zero where map_mask is 0.
+enum { kForward = 0, kMasked = 1, kLast = 2 };
+struct LastOut {
+    float *zout;
+    const double *norm2;
+    const uint8_t *map_mask;
+};
+template <int kMode>
+__global__ __launch_bounds__(kThreads) void k_conv16z(const uint16_t *__restrict__ in,
                                                       const bf16x8 *__restrict__ frag,
-                                                      const float *__restrict__ bias, Vol d,
-                                                      uint16_t *__restrict__ out, const int *__restrict__ skip)
+                                                      const float *__restrict__ bias, Vol d, March m,
+                                                      const uint16_t *__restrict__ mask,
+                                                      uint16_t *__restrict__ out, LastOut last,
+                                                      const int *__restrict__ skip)
 {
-    __shared__ uint4 buf0[kSlots];
-    __shared__ uint4 buf1[kSlots];
+    __shared__ uint4 buf[4][2 * kZPlane];
     if (skip && *skip) return;
+    int cx, cy, z0, z1;
+    if (!march_place(m, d, cx, cy, z0, z1)) return;
+    const int x0 = cx * kZX, y0 = cy * kZY;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const auto rs = make_rsrc(in, (uint32_t)(d.n * kC * 2));
+    const uint32_t plane_bytes = (uint32_t)(d.nx * d.ny) * (kC * 2);
+    // this lane's in-plane offsets of the staging loads (or the marker)
+    constexpr uint32_t kOut = 0xFFFFFFF0u;
+    uint32_t poff[kZLoads];
+#pragma unroll
+    for (int u = 0; u < kZLoads; ++u) {
+        const int sl = (u * (kThreads / 64) + wave) * 64 + lane;
+        const int h = sl >= kZPlane ? 1 : 0, rv = sl - h * kZPlane;
+        const int gx = x0 + rv % kZR - 1, gy = y0 + rv / kZR - 1;
+        const bool ok = sl < 2 * kZPlane && gx >= 0 && gx < d.nx && gy >= 0 && gy < d.ny;
+        poff[u] = ok ? (uint32_t)(gy * d.nx + gx) * (kC * 2) + h * 16 : kOut;
+    }
+    auto stage = [&](int z) {
+        const bool zin = z >= 0 && z < d.nz;
+        const uint32_t zo = zin ? (uint32_t)z * plane_bytes : 0u;
+#pragma unroll
+        for (int u = 0; u < kZLoads; ++u) {
+            const int c = u * (kThreads / 64) + wave;
+            if (c * 64 + lane < 2 * kZPlane) {
+                const uint32_t off = zin && poff[u] != kOut ? poff[u] + zo : kOut;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rs, (__attribute__((address_space(3))) void *)(&buf[z & 3][c * 64]), 16, (int)off, 0, 0, 0);
+            }
+        }
+    };
     bf16x8 w[kTriples];
     bf16x4 wt[kTriples];
     load_conv_frags(frag, lane, w, wt);
     const int vl = lane % 16, g = lane / 16, cg = 4 * g;
-    const ConvOffsets o = conv_offsets(vl, wave, g);
-    float b[4];
+    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (kMode == kForward) b = f32x4{bias[cg], bias[cg + 1], bias[cg + 2], bias[cg + 3]};
+    const float scale = kMode == kLast ? read_scale(last.norm2) : 1.0f, b3 = kMode == kLast ? bias[0] : 0.0f;
+    // byte offsets of the B operands for input row 4 * wave of a plane
+    const uint32_t o32 = (uint32_t)(((g & 1) * kZPlane + 4 * wave * kZR + vl + (g >> 1)) * 16);
+    const uint32_t o16 = (uint32_t)(((g >> 1) * kZPlane + 4 * wave * kZR + vl + 2) * 16 + (g & 1) * 8);
+    const int xo = x0 + vl;
+    bf16x4 res[kTY];
+    float res3[kTY];
+    auto store = [&](int z) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) b[r] = bias[cg + r];
-    pipelined_tiles(in, d, buf0, buf1, [&](const uint4 *region, int x0, int y0, int z0) {
+        for (int y = 0; y < kTY; ++y) {
+            const int yo = y0 + 4 * wave + y;
+            if (xo >= d.nx || yo >= d.ny) continue;
+            const int64_t vo = ((int64_t)z * d.ny + yo) * d.nx + xo;
+            if constexpr (kMode != kLast) {
+                *reinterpret_cast<bf16x4 *>(out + vo * kC + cg) = res[y];
+            } else if (lane < 16) {
+                last.zout[vo] = last.map_mask && !last.map_mask[vo] ? 0.0f : res3[y];
+            }
+        }
+    };
+    stage(z0 - 1);
+    stage(z0);
+    stage(z0 + 1);
+    for (int z = z0; z < z1; ++z) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();  // planes z-1..z+1 published; every wave past the plane whose buffer is staged next
+        if (z > z0) store(z - 1);
+        bf16x4 mk[kTY];
+        if constexpr (kMode == kMasked)
+#pragma unroll
+            for (int y = 0; y < kTY; ++y) {
+                const int yo = y0 + 4 * wave + y;
+                mk[y] = bf16x4{0, 0, 0, 0};
+                if (xo < d.nx && yo < d.ny)
+                    mk[y] = *reinterpret_cast<const bf16x4 *>(mask + (((int64_t)z * d.ny + yo) * d.nx + xo) * kC + cg);
+            }
+        if (z + 2 <= z1) stage(z + 2);
         f32x4 acc[kTY];
 #pragma unroll
         for (int y = 0; y < kTY; ++y) acc[y] = f32x4{0.f, 0.f, 0.f, 0.f};
-        conv_rows(reinterpret_cast<const char *>(region), o, w, wt, acc);
-        conv16_store(acc, b, d, x0, y0, z0, 1, nullptr, out);
-    });
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz) {
+            const char *rb = reinterpret_cast<const char *>(buf[(z - 1 + dz) & 3]);
+            bf16x8 b32[kRY];
+            bf16x4 b16[kRY];
+#pragma unroll
+            for (int yi = 0; yi < kRY; ++yi) {
+                b32[yi] = *reinterpret_cast<const bf16x8 *>(rb + o32 + yi * kZR * 16);
+                b16[yi] = *reinterpret_cast<const bf16x4 *>(rb + o16 + yi * kZR * 16);
+            }
+            conv_plane(b32, b16, dz, w, wt, acc);
+        }
+#pragma unroll
+        for (int y = 0; y < kTY; ++y) {
+            if constexpr (kMode == kLast) {
+                res3[y] = scale * ((acc[y][0] + acc[y][1]) + b3);
+                continue;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float val = acc[y][r];
+                if constexpr (kMode == kMasked) val = bf2f((uint16_t)mk[y][r]) > 0.0f ? val : 0.0f;
+                else val = fmaxf(val + b[r], 0.0f);
+                res[y][r] = (short)f2bf(val);
+            }
+        }
+    }
+    store(z1 - 1);
 }
 
-// Persistent 16 -> 1 layer (the inference forward's layer 3).
-__global__ __launch_bounds__(kThreads) void k_conv3p(const bf16x8 *__restrict__ frag3,
-                                                     const float *__restrict__ P,
-                                                     const uint16_t *__restrict__ a2, Vol d,
-                                                     const double *__restrict__ norm2,
-                                                     const uint8_t *__restrict__ map_mask,
-                                                     float *__restrict__ out, const int *__restrict__ skip)
+// layer 1: a1[v][c] = relu(b1[c] + sum_t w1[c][t] x[v + t - 1] / s), on MFMA
+// with the taps as the contraction index (k = tap, 27-31 with zero weight), by
+// 16 x 16 columns.  Weights and inputs are each split into a BF16 value and a
+// BF16 remainder, and the three products that matter (hi hi, hi lo, lo hi) keep
+// ~16 significant bits: three v_mfma_f32_16x16x32_bf16 per 16-voxel row.  The
+// scaled and split input planes go through an LDS ring of four.  A plane's values are loaded into
+// registers two planes ahead of their use, so the loop waits for no fresh load.
+// The ring turns with z: a lane's eight tap offsets are kept for its four
+// positions, and the loop body holds four planes.
+// 128^3: 21.7 us (29.8 with one 16 x 4 x 4 tile per workgroup, each tap's input
+// split where it was read); writing a1 alone takes about 10 us.
+constexpr int kZ1Loads = (kZPlane + kThreads - 1) / kThreads;
+__global__ __launch_bounds__(kThreads) void k_conv1z(const bf16x8 *__restrict__ frag1, const float *__restrict__ P,
+                                                     const float *__restrict__ x, Vol d, March m,
+                                                     const double *__restrict__ norm2, uint16_t *__restrict__ a1,
+                                                     const int *__restrict__ skip)
 {
-    __shared__ uint4 buf0[kSlots];
-    __shared__ uint4 buf1[kSlots];
+    __shared__ uint32_t xs[4][kZPlane];
     if (skip && *skip) return;
+    int cx, cy, z0, z1;
+    if (!march_place(m, d, cx, cy, z0, z1)) return;
     const float s = read_scale(norm2);
+    const float inv = s > 0.0f ? 1.0f / s : 0.0f;
+    const int x0 = cx * kZX, y0 = cy * kZY;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    bf16x8 w[kTriples];
-    bf16x4 wt[kTriples];
-    load_conv_frags(frag3, lane, w, wt);
-    const int vl = lane % 16, g = lane / 16;
-    const ConvOffsets o = conv_offsets(vl, wave, g);
-    const float b3 = P[OB3];
-    pipelined_tiles(a2, d, buf0, buf1, [&](const uint4 *region, int x0, int y0, int z0) {
-        f32x4 acc[kTY];
+    int64_t poff[kZ1Loads];  // in-plane offset of this thread's staged voxels (-1: outside)
 #pragma unroll
-        for (int y = 0; y < kTY; ++y) acc[y] = f32x4{0.f, 0.f, 0.f, 0.f};
-        conv_rows(reinterpret_cast<const char *>(region), o, w, wt, acc);
-        conv3_store(acc, s, b3, d, x0, y0, z0, map_mask, out);
-    });
+    for (int u = 0; u < kZ1Loads; ++u) {
+        const int e = u * kThreads + threadIdx.x;
+        const int gx = x0 + e % kZR - 1, gy = y0 + e / kZR - 1;
+        poff[u] = e < kZPlane && gx >= 0 && gx < d.nx && gy >= 0 && gy < d.ny ? (int64_t)gy * d.nx + gx : -1;
+    }
+    const int64_t plane = (int64_t)d.nx * d.ny;
+    auto load = [&](int z, float (&v)[kZ1Loads]) {
+#pragma unroll
+        for (int u = 0; u < kZ1Loads; ++u) {
+            v[u] = 0.0f;
+            if (z >= 0 && z < d.nz && poff[u] >= 0) v[u] = x[(int64_t)z * plane + poff[u]];
+        }
+    };
+    auto put = [&](int slot, const float (&v)[kZ1Loads]) {
+#pragma clang fp contract(off)  // the remainder is that of the rounded product
+#pragma unroll
+        for (int u = 0; u < kZ1Loads; ++u) {
+            const int e = u * kThreads + threadIdx.x;
+            const float t = v[u] * inv;
+            const uint16_t h = f2bf(t);
+            if (e < kZPlane) xs[slot][e] = (uint32_t)h << 16 | f2bf(t - bf2f(h));
+        }
+    };
+    const bf16x8 wh = frag1[lane], wl = frag1[64 + lane];
+    const int vl = lane % 16, g = lane / 16, cg = 4 * g;
+    // word offsets of taps 8g..8g+7 for output row 4 * wave when plane z - 1
+    // sits in ring slot ph; taps past 26 read tap 26 (zero weight)
+    int off[4][8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int t = min(8 * g + e, kTaps - 1);
+#pragma unroll
+        for (int ph = 0; ph < 4; ++ph)
+            off[ph][e] = ((ph + t / 9) & 3) * kZPlane + (4 * wave + (t / 3) % 3) * kZR + vl + t % 3;
+    }
+    float b[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) b[r] = P[OB1 + cg + r];
+    const uint32_t *ring = &xs[0][0];
+    const int xo = x0 + vl;
+    float v0[kZ1Loads], v1[kZ1Loads];
+    // planes z0 - 1 and z0 go to slots 0 and 1; z0 + 1 and z0 + 2 follow in the loop
+    load(z0 - 1, v0);
+    load(z0, v1);
+    put(0, v0);
+    put(1, v1);
+    load(z0 + 1, v0);
+    load(z0 + 2, v1);
+    auto step = [&](auto phase, int z, float (&v)[kZ1Loads]) {
+        constexpr int ph = decltype(phase)::value;
+        put((ph + 2) & 3, v);  // plane z + 1: its slot held plane z - 3
+        __syncthreads();       // (every wave is past plane z - 1's products, which read no other slot)
+        load(z + 3, v);
+#pragma unroll
+        for (int y = 0; y < kTY; ++y) {
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t p = ring[off[ph][2 * e] + y * kZR], q = ring[off[ph][2 * e + 1] + y * kZR];
+                hi[e] = __builtin_amdgcn_perm(q, p, 0x07060302u);
+                lo[e] = __builtin_amdgcn_perm(q, p, 0x05040100u);
+            }
+            const bf16x8 xh = __builtin_bit_cast(bf16x8, hi), xl = __builtin_bit_cast(bf16x8, lo);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh, xh, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wh, xl, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wl, xh, acc, 0, 0, 0);
+            const int yo = y0 + 4 * wave + y;
+            if (xo < d.nx && yo < d.ny) {
+                bf16x4 o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] = (short)f2bf(fmaxf(acc[r] + b[r], 0.0f));
+                *reinterpret_cast<bf16x4 *>(a1 + (((int64_t)z * d.ny + yo) * d.nx + xo) * kC + cg) = o;
+            }
+        }
+    };
+    for (int z = z0;; z += 4) {
+        step(std::integral_constant<int, 0>{}, z, v0);
+        if (z + 1 >= z1) break;
+        step(std::integral_constant<int, 1>{}, z + 1, v1);
+        if (z + 2 >= z1) break;
+        step(std::integral_constant<int, 2>{}, z + 2, v0);
+        if (z + 3 >= z1) break;
+        step(std::integral_constant<int, 3>{}, z + 3, v1);
+        if (z + 4 >= z1) break;
+    }
 }
 
 // ------------------------------------------------------------ training
@@ -791,10 +886,10 @@ static dim3 tile_grid(const Vol &d)
                 (unsigned)((d.nz + kTZ - 1) / kTZ));
 }
 
-// Workgroups of a persistent forward kernel: as many as stay resident on the
-// device (occupancy x compute units, queried once per kernel), at most one
-// per tile.
-static unsigned persistent_grid(const void *kernel, int64_t tiles)
+// Launch of a marching kernel over columns of cx x cy outputs: as many planes
+// per workgroup as leave about one round of the workgroups that stay resident
+// on the device (occupancy x compute units, queried once per kernel).
+static unsigned march_grid(const void *kernel, const Vol &d, int cx, int cy, March &m)
 {
     static std::mutex mu;
     static std::map<const void *, int64_t> resident;
@@ -813,7 +908,51 @@ static unsigned persistent_grid(const void *kernel, int64_t tiles)
             resident[kernel] = r;
         }
     }
-    return (unsigned)(tiles < r ? (tiles > 0 ? tiles : 1) : r);
+    m.ncx = (d.nx + cx - 1) / cx;
+    m.ncy = (d.ny + cy - 1) / cy;
+    const int64_t cols = (int64_t)m.ncx * m.ncy;
+    int64_t chunks = r / cols;
+    chunks = chunks < 1 ? 1 : (chunks > d.nz ? d.nz : chunks);
+    m.cz = (int32_t)((d.nz + chunks - 1) / chunks);
+    return (unsigned)(cols * ((d.nz + m.cz - 1) / m.cz));
+}
+
+// The layers on a stored activation: the marching kernels, or one tile per
+// workgroup where an activation passes the marching kernel's reach.
+template <int kMode>
+static void launch_conv16(const uint16_t *in, const bf16x8 *frag, const float *bias, const Vol &d,
+                          const uint16_t *mask, uint16_t *out, const int *skip, hipStream_t s)
+{
+    if (d.n <= kMaxMarchVoxels) {
+        March m;
+        const unsigned nb = march_grid(reinterpret_cast<const void *>(k_conv16z<kMode>), d, kZX, kZY, m);
+        hipLaunchKernelGGL(k_conv16z<kMode>, dim3(nb), dim3(kThreads), 0, s, in, frag, bias, d, m, mask, out,
+                           LastOut{}, skip);
+    } else {
+        hipLaunchKernelGGL(k_conv16, tile_grid(d), dim3(kThreads), 0, s, in, frag, bias, d, kMode == kForward ? 1 : 0,
+                           mask, out, skip);
+    }
+}
+
+static void launch_conv1(const bf16x8 *frag1, const float *P, const float *x, const Vol &d, const double *norm2,
+                         uint16_t *a1, const int *skip, hipStream_t s)
+{
+    March m;
+    const unsigned nb = march_grid(reinterpret_cast<const void *>(k_conv1z), d, kZX, kZY, m);
+    hipLaunchKernelGGL(k_conv1z, dim3(nb), dim3(kThreads), 0, s, frag1, P, x, d, m, norm2, a1, skip);
+}
+
+static void launch_conv3(const bf16x8 *frag3, const float *P, const uint16_t *a2, const Vol &d, const double *norm2,
+                         const uint8_t *map_mask, float *out, const int *skip, hipStream_t s)
+{
+    if (d.n <= kMaxMarchVoxels) {
+        March m;
+        const unsigned nb = march_grid(reinterpret_cast<const void *>(k_conv16z<kLast>), d, kZX, kZY, m);
+        hipLaunchKernelGGL(k_conv16z<kLast>, dim3(nb), dim3(kThreads), 0, s, a2, frag3, P + OB3, d, m,
+                           (const uint16_t *)nullptr, (uint16_t *)nullptr, LastOut{out, norm2, map_mask}, skip);
+    } else {
+        hipLaunchKernelGGL(k_conv3, tile_grid(d), dim3(kThreads), 0, s, frag3, P, a2, d, norm2, map_mask, out, skip);
+    }
 }
 
 static unsigned vox_blocks(int64_t n)
@@ -836,21 +975,9 @@ int convnet_forward_dev(const tomo_cube &c, const float *P, const float *x, floa
     bf16x8 *frag = (bf16x8 *)(base + 2 * align256(sizeof(uint16_t) * kC * d.n));
     if (prep_frags)
         hipLaunchKernelGGL(k_conv_frags, dim3((kFragFwd + 255) / 256), dim3(256), 0, s, P, 0, frag);
-    hipLaunchKernelGGL(k_conv1, tile_grid(d), dim3(kThreads), 0, s, frag + kFrag1, P, x, d, norm2, a1, skip);
-    if (d.n <= kMaxPipelinedVoxels) {  // persistent, pipelined layers 2 and 3
-        const dim3 tg = tile_grid(d);
-        const int64_t tiles = (int64_t)tg.x * tg.y * tg.z;
-        const unsigned g16 = persistent_grid(reinterpret_cast<const void *>(k_conv16p), tiles);
-        const unsigned g3 = persistent_grid(reinterpret_cast<const void *>(k_conv3p), tiles);
-        hipLaunchKernelGGL(k_conv16p, dim3(g16), dim3(kThreads), 0, s, a1, frag, P + OB2, d, a2, skip);
-        hipLaunchKernelGGL(k_conv3p, dim3(g3), dim3(kThreads), 0, s, frag + kFrag3, P, a2, d, norm2, map_mask, out,
-                           skip);
-    } else {
-        hipLaunchKernelGGL(k_conv16, tile_grid(d), dim3(kThreads), 0, s, a1, frag, P + OB2, d, 1,
-                           (const uint16_t *)nullptr, a2, skip);
-        hipLaunchKernelGGL(k_conv3, tile_grid(d), dim3(kThreads), 0, s, frag + kFrag3, P, a2, d, norm2, map_mask,
-                           out, skip);
-    }
+    launch_conv1(frag + kFrag1, P, x, d, norm2, a1, skip, s);
+    launch_conv16<kForward>(a1, frag, P + OB2, d, nullptr, a2, skip, s);
+    launch_conv3(frag + kFrag3, P, a2, d, norm2, map_mask, out, skip, s);
     return hip_fail(hipGetLastError(), "convnet forward launch");
 }
 
@@ -900,18 +1027,14 @@ static int convnet_train_pass(const tomo_cube *cube, const float *params_d, cons
     NetWs w;
     ws_layout(n, &w, (char *)ws_d);
     const Vol d{cube->nx, cube->ny, cube->nz, n};
-    const dim3 rowgrid = tile_grid(d);
     // forward, keeping activations
     hipLaunchKernelGGL(k_conv_frags, dim3((kFragFwd + 255) / 256), dim3(256), 0, s, params_d, 0, w.frag);
     hipLaunchKernelGGL(k_conv_frags, dim3((kFragConv + 255) / 256), dim3(256), 0, s, params_d, 1, w.fragT);
     const int *noskip = nullptr;
-    hipLaunchKernelGGL(k_conv1, rowgrid, dim3(kThreads), 0, s, w.frag + kFrag1, params_d, x_d, d,
-                       (const double *)nullptr, w.a1, noskip);
-    hipLaunchKernelGGL(k_conv16, rowgrid, dim3(kThreads), 0, s, w.a1, w.frag, params_d + OB2, d, 1,
-                       (const uint16_t *)nullptr, w.a2, noskip);
+    launch_conv1(w.frag + kFrag1, params_d, x_d, d, nullptr, w.a1, noskip, s);
+    launch_conv16<kForward>(w.a1, w.frag, params_d + OB2, d, nullptr, w.a2, noskip, s);
     if (target_d) {
-        hipLaunchKernelGGL(k_conv3, rowgrid, dim3(kThreads), 0, s, w.frag + kFrag3, params_d, w.a2, d,
-                           (const double *)nullptr, (const uint8_t *)nullptr, w.out, noskip);
+        launch_conv3(w.frag + kFrag3, params_d, w.a2, d, nullptr, nullptr, w.out, noskip, s);
         // loss and d loss / d out
         hipLaunchKernelGGL(k_mse, dim3(kLossBlocks), dim3(kThreads), 0, s, w.out, target_d, n, w.g,
                            w.loss_part);
@@ -926,8 +1049,7 @@ static int convnet_train_pass(const tomo_cube *cube, const float *params_d, cons
     hipLaunchKernelGGL(k_reduce_parts, dim3((6928 + 255) / 256), dim3(256), 0, s, w.part, kWgBlocks, 6928,
                        grad_d, OW2);
     // d loss / d h1 = [a1 > 0] conv^T(gh); written over a2 (no longer needed)
-    hipLaunchKernelGGL(k_conv16, rowgrid, dim3(kThreads), 0, s, w.gh, w.fragT, (const float *)nullptr, d,
-                       0, w.a1, w.a2, noskip);
+    launch_conv16<kMasked>(w.gh, w.fragT, nullptr, d, w.a1, w.a2, noskip, s);
     // layer 1
     hipLaunchKernelGGL(k_wgrad1, dim3(kWgBlocks), dim3(448), 0, s, w.a2, x_d, d, w.part);
     hipLaunchKernelGGL(k_reduce_parts, dim3(2), dim3(256), 0, s, w.part, kWgBlocks, 448, grad_d, OW1);
