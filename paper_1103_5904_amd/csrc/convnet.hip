@@ -201,8 +201,8 @@ __device__ inline ConvOffsets conv_offsets(int vl, int lz, int g)
 // three independent MFMA instructions separate two that update the same
 // accumulator: an instruction then never reads as its accumulator input the
 // result of one still in flight.
-__device__ inline void conv_plane(const bf16x8 (&b32)[kRY], const bf16x4 (&b16)[kRY], int dz,
-                                  const bf16x8 (&w)[kTriples], const bf16x4 (&wt)[kTriples], f32x4 (&acc)[kTY])
+// The K = 32 part of x-triples 3 dz .. 3 dz + 2.
+__device__ inline void conv_k32(const bf16x8 (&b32)[kRY], int dz, const bf16x8 (&w)[kTriples], f32x4 (&acc)[kTY])
 {
 #pragma unroll
     for (int dy = 0; dy < 3; ++dy) {
@@ -211,6 +211,11 @@ __device__ inline void conv_plane(const bf16x8 (&b32)[kRY], const bf16x4 (&b16)[
             acc[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[3 * dz + dy], b32[y + dy], acc[y], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);  // keep the four-row interleave as written
     }
+}
+
+// The K = 16 part of the same triples.
+__device__ inline void conv_k16(const bf16x4 (&b16)[kRY], int dz, const bf16x4 (&wt)[kTriples], f32x4 (&acc)[kTY])
+{
 #pragma unroll
     for (int dy = 0; dy < 3; ++dy) {
 #pragma unroll
@@ -233,7 +238,8 @@ __device__ inline void conv_rows(const char *rbytes, const ConvOffsets &o, const
             b32[yi] = *reinterpret_cast<const bf16x8 *>(rbytes + o.k32 + row);
             b16[yi] = *reinterpret_cast<const bf16x4 *>(rbytes + o.k16 + row);
         }
-        conv_plane(b32, b16, dz, w, wt, acc);
+        conv_k32(b32, dz, w, acc);
+        conv_k16(b16, dz, wt, acc);
     }
 }
 
@@ -409,11 +415,12 @@ constexpr int64_t kMaxMarchVoxels = ((int64_t)1 << 27) - 1;
 // computes four rows per plane with conv_rows' arithmetic and order, and
 // stores them after the next plane's barrier, so that the wait for the
 // arriving plane never waits for a fresh store.
-// 128^3: layer 2 35.9 us (40.7 with persistent 16 x 4 x 4 tiles, 2.53 reads per
-// input voxel), its data gradient 39.5 (61.3), layer 3 32.4 (37.1).  The MFMA
+// 128^3: layer 2 34.2 us (40.7 with persistent 16 x 4 x 4 tiles, 2.53 reads per
+// input voxel), its data gradient 39.1 (61.3), layer 3 30.4 (37.1).  The MFMA
 // pipe is busy for 15 us of each and LDS reads take as long, in phases that
-// the three workgroups of a CU overlap in part.  Prefetching the next plane's
-// operands into registers cost the third workgroup and won nothing.
+// the three workgroups of a CU overlap in part (35.9 and 32.4 before the reads
+// were issued one group of products ahead; a whole plane ahead costs the
+// third workgroup its registers and wins nothing).
 // kMode: what the products become.
 //   kForward: out = ReLU(bias + conv);
 //   kMasked: out = conv where mask > 0, else 0 (the data gradient through the
@@ -513,17 +520,26 @@ __global__ __launch_bounds__(kThreads) void k_conv16z(const uint16_t *__restrict
         f32x4 acc[kTY];
 #pragma unroll
         for (int y = 0; y < kTY; ++y) acc[y] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // operands are read one group ahead: a plane's K = 16 operands under its
+        // K = 32 products, the next plane's K = 32 operands under the K = 16 ones
+        bf16x8 b32[kRY];
+        bf16x4 b16[kRY];
+        auto rows = [&](int dz) { return reinterpret_cast<const char *>(buf[(z - 1 + dz) & 3]); };
+        auto fetch32 = [&](const char *rb) {
+#pragma unroll
+            for (int yi = 0; yi < kRY; ++yi) b32[yi] = *reinterpret_cast<const bf16x8 *>(rb + o32 + yi * kZR * 16);
+        };
+        fetch32(rows(0));
 #pragma unroll
         for (int dz = 0; dz < 3; ++dz) {
-            const char *rb = reinterpret_cast<const char *>(buf[(z - 1 + dz) & 3]);
-            bf16x8 b32[kRY];
-            bf16x4 b16[kRY];
+            const char *rb = rows(dz);
 #pragma unroll
-            for (int yi = 0; yi < kRY; ++yi) {
-                b32[yi] = *reinterpret_cast<const bf16x8 *>(rb + o32 + yi * kZR * 16);
-                b16[yi] = *reinterpret_cast<const bf16x4 *>(rb + o16 + yi * kZR * 16);
-            }
-            conv_plane(b32, b16, dz, w, wt, acc);
+            for (int yi = 0; yi < kRY; ++yi) b16[yi] = *reinterpret_cast<const bf16x4 *>(rb + o16 + yi * kZR * 16);
+            __builtin_amdgcn_sched_barrier(0);
+            conv_k32(b32, dz, w, acc);
+            if (dz < 2) fetch32(rows(dz + 1));
+            __builtin_amdgcn_sched_barrier(0);
+            conv_k16(b16, dz, wt, acc);
         }
 #pragma unroll
         for (int y = 0; y < kTY; ++y) {
