@@ -220,7 +220,7 @@ int tomo_trace_ray(const tomo_geometry *g, int32_t view, int32_t col,
  *     order and takes no bundle shape).
  *   p_xcd_remap, bp_xcd_remap: order of the tiles (of the voxel-block items
  *     for the blocked back-projection) over the 8 XCDs: 0 = launch order,
- *     1 = one contiguous run per XCD, 2 = runs of 64 per XCD with all XCDs
+ *     1 = one contiguous run per XCD, 2 = runs of 32 per XCD with all XCDs
  *     advancing through the list together (a multi-frame cube then keeps one
  *     frame in the caches at a time).
  *   bp_lds_bins: 64-bit LDS bins per workgroup of the binned
@@ -247,6 +247,11 @@ int tomo_trace_ray(const tomo_geometry *g, int32_t view, int32_t col,
  *     the cube; it pays where the cube is far larger than the caches and
  *     the rays are sparser than the voxels, so that a ray's consecutive
  *     gathers would otherwise each fetch a cache line of their own.
+ *     While p_bundle, p_xcd_remap and p_layout hold their initial values (2,
+ *     1, 0) together, every geometry takes the three that suit its cube and
+ *     pixels (tomo_get_class_tuning reports them); the results are the same
+ *     bit for bit.  A tomo_project under stream capture then walks the
+ *     caller's array.
  *   bp_ray_table: 1 = where one geometry serves several blocked
  *     back-projections (tomo_cg_solve, a batch), its rays are set up once
  *     into a table (96 bytes per pixel: in the solve's scratch or workspace,

@@ -37,6 +37,52 @@ tomo_tuning current_tuning()
     return g_tuning;
 }
 
+tomo_tuning untuned_for(const Plan &p)
+{
+    tomo_tuning t = current_tuning();
+    if (t.p_bundle == 2 && t.p_xcd_remap == 1 && t.p_layout == 0) {
+        t.p_bundle = p.p_auto[0];
+        t.p_xcd_remap = p.p_auto[1];
+        t.p_layout = p.p_auto[2];
+    }
+    return t;
+}
+
+// P's bundle, tile order and cube layout for a geometry, from MI355X times of
+// single calls (their brick copy included; x-fastest walk with 4x16 bundles
+// against bricks).  The x-fastest walk is bound by the lines its gathers touch
+// (about 26 per wavefront where pixels are finer than voxels), and it suits a
+// cube that an XCD's 4 MiB L2 holds; above that, and once the walk outweighs
+// the copy (6 crossings per voxel):
+// - lines of sight closer than 2.5 to a voxel's smallest side: bricks of 4^3
+//   (a 128-byte line is 4x4x2 voxels) and 8x8 bundles.  256^3 under 64 x 256^2:
+//   4.00 -> 1.36 ms; one 256^3 frame under 60 x 512^2: 4.77 -> 1.83; 128^3 under
+//   32 x 256^2: 0.35 -> 0.19; 64x256x128 under 20 x 256^2: 0.36 -> 0.17.  Denser
+//   lines share the x-fastest lines well (193x150x77 under 20 x 512^2: 0.449
+//   against 0.458; 120x110x100 under 28 x 512^2: 0.419 against 0.457), unless
+//   rows of a multiple of 128 bytes put a plane's rows on the same cache sets
+//   (128^3 under 28 x 512^2: 0.73 -> 0.51; 160^3 under 20 x 1024^2: 2.00 -> 1.54);
+// - sparser than 0.7 voxels: lines of sight share no lines, and a line that is
+//   flat in z and long in x serves the longest run of one ray: bricks of 8^3
+//   and 16x4 bundles.  512^3 under 64 x 256^2: 13.2 -> 6.9 ms (4^3: 11.4); 256^3
+//   under 64 x 128^2: 1.32 -> 0.79 (4^3: 1.03).  At 0.8 the two are even.
+// Fewer crossings than the copy is worth: 320x280x300 under 60 x 60^2 (3.6 per
+// voxel) 0.48 ms x-fastest, 0.52 from bricks.
+static void p_defaults(const tomo_geometry *g, int64_t npix, const GridDev &gd, double rays_per_voxel, int32_t (&out)[3])
+{
+    const double steps = 0.5 * (double)npix * ((double)gd.n[0] + gd.n[1] + gd.n[2]);
+    if (gd.nvox < ((int64_t)1 << 20) || steps < 6.0 * (double)gd.nvox * gd.nframes) return;
+    if (rays_per_voxel < 0.7) {
+        out[0] = 4;
+        out[1] = 2;
+        out[2] = 3;
+    } else if (rays_per_voxel < 2.5 || g->cube.nx % 32 == 0) {
+        out[0] = 3;
+        out[1] = 2;
+        out[2] = 2;
+    }
+}
+
 int set_error(int status, const char *fmt, ...)
 {
     char buf[512];
@@ -228,7 +274,10 @@ static int build_plan(const tomo_geometry *g, int64_t npix, Plan &p)
             ratio[(size_t)k] = px > 0.0 ? vox / px : 0.0;
         }
         std::nth_element(ratio.begin(), ratio.begin() + ratio.size() / 2, ratio.end());
-        p.bp_rows = ratio[ratio.size() / 2] >= 1.4;
+        const double med = ratio[ratio.size() / 2];
+        p.bp_rows = med >= 1.4;
+        const double side = std::min(gd.delta[0], std::min(gd.delta[1], gd.delta[2]));
+        p_defaults(g, npix, gd, med * side / vox, p.p_auto);
     }
     hipError_t e = hipMalloc((void **)&p.views_d, sizeof(ViewDev) * hv.size());
     if (e != hipSuccess) return set_error(TOMO_ENOMEM, "view table allocation: %s", hipGetErrorString(e));

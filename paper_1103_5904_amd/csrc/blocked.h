@@ -8,13 +8,9 @@ namespace tomo {
 
 constexpr int kYmaxParts = 64;  // partial maxima per view (64 workgroups per view keep the pass short)
 
-// LDS byte address of a pointer into shared memory, and atomic adds at such
-// an address: a walk that carries its bin as an address needs no shift or
-// base add per step (the clamp's result is the instruction's address).
-__device__ inline uint32_t lds_address(const void *p)
-{
-    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)p;
-}
+// Atomic adds at an LDS byte address: a walk that carries its bin as an
+// address needs no shift or base add per step (the clamp's result is the
+// instruction's address).
 __device__ inline void lds_add_u64(uint32_t a, unsigned long long v)
 {
     __hip_atomic_fetch_add((__attribute__((address_space(3))) unsigned long long *)(uintptr_t)a, v,

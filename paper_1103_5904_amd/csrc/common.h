@@ -106,7 +106,7 @@ __device__ inline int64_t xcd_remap(int64_t b, int64_t nb)
 // frame of a multi-frame cube, not eight), while each XCD's L2 still sees
 // neighbouring tiles.  The ragged last group keeps the identity.  Bijective
 // on [0, nb).
-constexpr int64_t kXcdChunk = 64;
+constexpr int64_t kXcdChunk = 32;
 __device__ inline int64_t xcd_remap_chunked(int64_t b, int64_t nb)
 {
     const int64_t g = b / (8 * kXcdChunk);
@@ -165,6 +165,7 @@ struct Plan {
     int32_t min_frame_views = 0;       // fewest views any frame has
     bool bp_rows = false;              // blocked P^T walks footprint row intervals (pixels finer than voxels)
     uint64_t size_class = 0;           // key of the autotuner's cache (size_class_of)
+    int32_t p_auto[3] = {2, 1, 0};     // P's bundle, tile order and cube layout where the tuning leaves them open
     Plan() = default;
     Plan(const Plan &) = delete;
     Plan &operator=(const Plan &) = delete;
@@ -193,8 +194,11 @@ hipError_t scratch_free(void *p, hipStream_t s);
 int validate_cube(const tomo_cube *c);
 tomo_tuning current_tuning();
 uint64_t size_class_of(const tomo_geometry *g, int64_t npix);
+// The process-wide tuning as it applies to this plan: with P's initial values
+// (2, 1, 0) untouched, P's shape and layout are the plan's own (p_auto).
+tomo_tuning untuned_for(const Plan &p);
 // The tuning launches on this plan use: its size class's autotuned entry if
-// there is one, else the process-wide tuning.
+// there is one, else untuned_for.
 tomo_tuning tuning_for(const Plan &p);
 
 // Per-ray results of the ray set-up over a whole geometry, for launches

@@ -246,7 +246,21 @@ int launch_project_tuned(const Plan &p, const tomo_geometry *g, const float *cub
 int launch_project(const Plan &p, const tomo_geometry *g, const float *cube, float *images,
                    bool use_map_mask, hipStream_t s)
 {
-    return launch_project_with(p, g, cube, images, use_map_mask, s, tuning_for(p));
+    tomo_tuning tu = tuning_for(p);
+    // a graph under capture holds no allocation of the library's own choosing
+    if (tu.p_layout >= 2 && current_tuning().p_layout == 0) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+        if (cap != hipStreamCaptureStatusNone) {
+            const tomo_tuning open = untuned_for(p);
+            if (open.p_layout == tu.p_layout && open.p_bundle == tu.p_bundle && open.p_xcd_remap == tu.p_xcd_remap) {
+                tu.p_bundle = 2;
+                tu.p_xcd_remap = 1;
+                tu.p_layout = 0;
+            }
+        }
+    }
+    return launch_project_with(p, g, cube, images, use_map_mask, s, tu);
 }
 
 // The bricked layout of a plan's frames for brick side 2^k, or false when a

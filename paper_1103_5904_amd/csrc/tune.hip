@@ -94,7 +94,7 @@ tomo_tuning tuning_for(const Plan &p)
         auto it = g_class_tuning.find(p.size_class);
         if (it != g_class_tuning.end()) return it->second;
     }
-    return current_tuning();
+    return untuned_for(p);
 }
 
 static int autotune_impl(const tomo_geometry *g, const float *cube_in, const float *img_in, int32_t reps,
@@ -109,7 +109,7 @@ static int autotune_impl(const tomo_geometry *g, const float *cube_in, const flo
     const bool wide = p.grid.nvox >= ((int64_t)1 << 30);  // the atomic strategies refuse such frames
 
     // candidates
-    const tomo_tuning base = current_tuning();
+    const tomo_tuning base = untuned_for(p);
     std::vector<tomo_tuning> pc, bc;
     for (int lay : {0, 2, 3, 4})
         for (int bun : {0, 2, 3, 4})
@@ -329,7 +329,7 @@ int tomo_get_class_tuning(const tomo_geometry *g, tomo_tuning *out, int32_t *tun
             found = true;
         }
     }
-    if (!found) *out = current_tuning();
+    if (!found) *out = untuned_for(*plan);
     if (tuned) *tuned = found ? 1 : 0;
     return TOMO_OK;
 }

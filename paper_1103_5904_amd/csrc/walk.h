@@ -19,6 +19,18 @@ struct RayState {
     int32_t st[3]; // signed flat stride of a step on each axis
 };
 
+// LDS byte address of a pointer into shared memory, and a read at such an
+// address: a walk that carries its table entry as an address needs no shift
+// or base add per step.
+__device__ inline uint32_t lds_address(const void *p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)p;
+}
+__device__ inline uint32_t lds_read_u32(uint32_t a)
+{
+    return *(__attribute__((address_space(3))) const uint32_t *)(uintptr_t)a;
+}
+
 __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // n / d from a reciprocal inv ~ 1/d and one residual correction: the
@@ -247,36 +259,260 @@ __device__ inline double tie_factor(bool t)
     return __builtin_bit_cast(double, (uint64_t)(t ? 0x3FF00000u : 0u) << 32);
 }
 
+// Advances every axis whose next crossing is m: s[a] += ds[a] and o += st[a]
+// where s[a] == m (exact on the common grid), the others left alone.  Written
+// under the execution mask (v_cmpx), three VALU instructions per axis, against
+// five for the same update by selects (a compare, a 0/1 factor and an FMA, a
+// select and an add), which the compiler makes of the plain condition; the
+// mask is saved and restored by scalar moves, which issue beside other waves'
+// VALU instructions.
+__device__ inline void advance(double (&s)[3], const double (&ds)[3], double m, uint32_t &o, const uint32_t (&st)[3])
+{
+    uint64_t sv;
+    asm("s_mov_b64 %[sv], exec\n\t"
+        "v_cmpx_eq_f64_e32 vcc, %[s0], %[m]\n\t"
+        "v_add_f64 %[s0], %[s0], %[d0]\n\t"
+        "v_add_u32_e32 %[o], %[o], %[t0]\n\t"
+        "s_mov_b64 exec, %[sv]\n\t"
+        "v_cmpx_eq_f64_e32 vcc, %[s1], %[m]\n\t"
+        "v_add_f64 %[s1], %[s1], %[d1]\n\t"
+        "v_add_u32_e32 %[o], %[o], %[t1]\n\t"
+        "s_mov_b64 exec, %[sv]\n\t"
+        "v_cmpx_eq_f64_e32 vcc, %[s2], %[m]\n\t"
+        "v_add_f64 %[s2], %[s2], %[d2]\n\t"
+        "v_add_u32_e32 %[o], %[o], %[t2]\n\t"
+        "s_mov_b64 exec, %[sv]"
+        : [s0] "+&v"(s[0]), [s1] "+&v"(s[1]), [s2] "+&v"(s[2]), [o] "+&v"(o), [sv] "=&s"(sv)
+        : [m] "v"(m), [d0] "v"(ds[0]), [d1] "v"(ds[1]), [d2] "v"(ds[2]), [t0] "v"(st[0]), [t1] "v"(st[1]),
+          [t2] "v"(st[2])
+        : "vcc");
+}
+
+// The same with one position per axis: i[a] += st[a] where s[a] == m.
+__device__ inline void advance(double (&s)[3], const double (&ds)[3], double m, uint32_t (&i)[3],
+                               const uint32_t (&st)[3])
+{
+    uint64_t sv;
+    asm("s_mov_b64 %[sv], exec\n\t"
+        "v_cmpx_eq_f64_e32 vcc, %[s0], %[m]\n\t"
+        "v_add_f64 %[s0], %[s0], %[d0]\n\t"
+        "v_add_u32_e32 %[i0], %[i0], %[t0]\n\t"
+        "s_mov_b64 exec, %[sv]\n\t"
+        "v_cmpx_eq_f64_e32 vcc, %[s1], %[m]\n\t"
+        "v_add_f64 %[s1], %[s1], %[d1]\n\t"
+        "v_add_u32_e32 %[i1], %[i1], %[t1]\n\t"
+        "s_mov_b64 exec, %[sv]\n\t"
+        "v_cmpx_eq_f64_e32 vcc, %[s2], %[m]\n\t"
+        "v_add_f64 %[s2], %[s2], %[d2]\n\t"
+        "v_add_u32_e32 %[i2], %[i2], %[t2]\n\t"
+        "s_mov_b64 exec, %[sv]"
+        : [s0] "+&v"(s[0]), [s1] "+&v"(s[1]), [s2] "+&v"(s[2]), [i0] "+&v"(i[0]), [i1] "+&v"(i[1]),
+          [i2] "+&v"(i[2]), [sv] "=&s"(sv)
+        : [m] "v"(m), [d0] "v"(ds[0]), [d1] "v"(ds[1]), [d2] "v"(ds[2]), [t0] "v"(st[0]), [t1] "v"(st[1]),
+          [t2] "v"(st[2])
+        : "vcc");
+}
+
+// The parameter of the walk's next event.  Without an obstacle the exit is
+// itself the crossing of the box's far face, which the exact increments
+// reach, so the three crossings bound it.
+template <bool kObstacle>
+__device__ inline double next_event(const double (&s)[3], double send)
+{
+    const double m = fmin(s[0], s[1]);
+    return kObstacle ? fmin(m, fmin(s[2], send)) : fmin(m, s[2]);
+}
+
 // Walk the ray voxel by voxel.  visit(off, dl) receives the flat voxel
-// offset and the parameter length of the segment (length = dl * |d|).
-// Simultaneous crossings advance every tied axis in one step.  maxit bounds
-// the loop whatever the arithmetic does; the loop body holds four steps, so
-// the bound is tested once per four (it may run up to three steps past it).
+// offset and the parameter length of the segment (length = dl * |d|).  Simultaneous crossings advance every tied
+// axis in one step.  maxit bounds the loop whatever the arithmetic does; the
+// loop body holds four steps, so the bound is tested once per four (it may
+// run up to three steps past it).
 template <class Visit>
 __device__ inline void ray_walk(RayState &r, int maxit, Visit &&visit)
 {
     double scur = 0.0;
-    // The state advances before the segment is visited, so that a gather
-    // of the segment's voxel (issued from its offset at the top of the
-    // step) has the tie updates to arrive in; after the last segment the
-    // advanced state is not used.
+    uint32_t o = (uint32_t)r.off;
+    const uint32_t st[3] = {(uint32_t)r.st[0], (uint32_t)r.st[1], (uint32_t)r.st[2]};
     auto step = [&]() {  // true once the ray has ended
-        const double m = fmin(fmin(r.s[0], r.s[1]), fmin(r.s[2], r.send));
-        const int32_t off = r.off;
-        const double dl = m - scur;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const bool t = (r.s[a] == m);
-            r.s[a] = fma(r.ds[a], tie_factor(t), r.s[a]);  // s + ds or s, exact on the common grid
-            r.off += t ? r.st[a] : 0;
-        }
+        const double m = next_event<true>(r.s, r.send);
+        visit((int32_t)o, m - scur);
+        advance(r.s, r.ds, m, o, st);
         scur = m;
-        visit(off, dl);
         return m >= r.send;
     };
     for (int it = 0; it < maxit; it += 4) {
         if (step() || step() || step() || step()) break;
     }
+}
+
+// Sum over the ray's segments of length x voxel value, in parameter units:
+// load(pos) issues the gather of the voxel at pos (an offset, or one position
+// per axis; st its steps) and value(.) turns what it loaded into the voxel's
+// value.  Pipelined by one segment: a step issues its voxel's gather before
+// it adds the previous segment, so two gathers are in flight per lane and
+// each has a whole step to land.  The two pending segments alternate between
+// the names a and b, and a lane that ends keeps both as they are, so no
+// register is copied (and no gather waited for) at the loop's back edge.
+template <bool kObstacle, class Pos, class Step, class Load, class Value>
+__device__ inline double ray_integrate(RayState &r, int maxit, Pos &pos, const Step &st, Load &&load, Value &&value)
+{
+    using T = decltype(load(pos));
+    double acc = 0.0, scur = 0.0, da = 0.0, db = 0.0;
+    T xa{}, xb{};
+    bool a_last = false;
+    auto step = [&](T &x, double &d, const T &x_prev, const double &d_prev) {  // true once the ray has ended
+        const double m = next_event<kObstacle>(r.s, r.send);
+        x = load(pos);
+        d = m - scur;
+        advance(r.s, r.ds, m, pos, st);
+        scur = m;
+        acc = fma(d_prev, value(x_prev), acc);
+        return m >= r.send;
+    };
+    for (int it = 0; it < maxit; it += 4) {
+        a_last = true;
+        if (step(xa, da, xb, db)) break;
+        a_last = false;
+        if (step(xb, db, xa, da)) break;
+        a_last = true;
+        if (step(xa, da, xb, db)) break;
+        a_last = false;
+        if (step(xb, db, xa, da)) break;
+    }
+    return a_last ? fma(da, value(xa), acc) : fma(db, value(xb), acc);
+}
+
+// ---- the two hot walks of P as one machine loop each.  What the compiler
+// makes of ray_integrate keeps the four exits of a body apart with mask
+// arithmetic, register copies and a wait for the newest gather; here a step
+// is fifteen VALU instructions and its gather (and, for bricked offsets, an
+// add and three LDS reads, each issued as soon as its axis' position is
+// known).  A step adds the segment of three steps before, so four gathers are
+// in flight per lane.  A lane that ends leaves the execution mask by the
+// compare that finds its end; the step's exit block, out of the loop's way,
+// adds the segments such lanes still have pending, oldest first.  Every load
+// is waited for inside the block.
+// Bound by VALU issue where lines of sight are dense (128^3 under 28 x 512^2
+// from 4^3 bricks: 0.505 ms, 0.87 of the issue ceiling; 23 to 26.5 VALU per
+// step and 0.76 ms from the x-fastest cube before), by L2 where they are as far
+// apart as voxels (256^3 under 64 x 256^2: 1.37 ms, 22 GB of lines from L2; 4.64
+// ms x-fastest).  One gather in flight less: 5% slower there, even elsewhere.
+//
+// Axis A's update where its crossing is the event M.  TERM reads the axis'
+// offset term for the next step.
+#define TOMO_AXIS(A, P, M, TERM)                        \
+    "v_cmpx_eq_f64_e32 vcc, %[s" A "], %[" M "]\n\t"    \
+    "v_add_f64 %[s" A "], %[s" A "], %[d" A "]\n\t"     \
+    "v_add_u32_e32 %[" P "], %[" P "], %[t" A "]\n\t"   \
+    "s_mov_b64 exec, %[sv]\n\t" TERM(A)
+// The same for the axis the lines of sight cross least (z: observers sit near
+// the ecliptic): the update is stepped over while no lane of the wave crosses.
+#define TOMO_AXIS_RARE(A, P, M, TERM, K)                \
+    "v_cmpx_eq_f64_e32 vcc, %[s" A "], %[" M "]\n\t"    \
+    "s_cbranch_execz .Ltomo_skip" K "_%=\n\t"           \
+    "v_add_f64 %[s" A "], %[s" A "], %[d" A "]\n\t"     \
+    "v_add_u32_e32 %[" P "], %[" P "], %[t" A "]\n"     \
+    ".Ltomo_skip" K "_%=:\n\t"                          \
+    "s_mov_b64 exec, %[sv]\n\t" TERM(A)
+// Adds segment Q (length e<Q>, voxel x<Q>) to the sum.
+#define TOMO_ADD(Q)                                     \
+    "v_cvt_f64_f32_e32 %[cv], %[x" Q "]\n\t"            \
+    "v_fma_f64 %[acc], %[e" Q "], %[cv], %[acc]\n\t"
+// Step K (0..3): the event's parameter M (the previous one's in MP), segment
+// K's gather and length; segment O, the oldest, is added.  MIN: the exit joins
+// the minimum (obstacle).
+#define TOMO_STEP(K, O, M, MP, MIN, LOAD, TERM, P0, P1, P2)          \
+    "v_min_f64 %[" M "], %[s0], %[s1]\n\t"                           \
+    "v_min_f64 %[" M "], %[" M "], %[s2]\n\t" MIN(M) LOAD("x" K)     \
+    "v_add_f64 %[e" K "], %[" M "], -%[" MP "]\n\t"                  \
+    "s_waitcnt vmcnt(3)\n\t" TOMO_ADD(O)                             \
+    "v_cmpx_lt_f64_e32 vcc, %[" M "], %[send]\n\t"                   \
+    "s_andn2_b64 %[tm], %[sv], exec\n\t"                             \
+    "s_cbranch_scc1 .Ltomo_exit" K "_%=\n"                           \
+    ".Ltomo_go" K "_%=:\n\t"                                         \
+    "s_mov_b64 %[sv], exec\n\t"                                      \
+    TOMO_AXIS("0", P0, M, TERM) TOMO_AXIS("1", P1, M, TERM) TOMO_AXIS_RARE("2", P2, M, TERM, K)
+// Exit block of step K for the lanes in tm: segments A, B and K.
+#define TOMO_EXIT(K, A, B)                              \
+    ".Ltomo_exit" K "_%=:\n\t"                          \
+    "s_mov_b64 %[sv], exec\n\t"                         \
+    "s_mov_b64 exec, %[tm]\n\t"                         \
+    "s_waitcnt vmcnt(0)\n\t"                            \
+    TOMO_ADD(A) TOMO_ADD(B) TOMO_ADD(K)                 \
+    "s_mov_b64 exec, %[sv]\n\t"                         \
+    "s_cbranch_execz .Ltomo_end_%=\n\t"                 \
+    "s_branch .Ltomo_go" K "_%=\n"
+#define TOMO_MIN_NONE(M) ""
+#define TOMO_MIN_EXIT(M) "v_min_f64 %[" M "], %[" M "], %[send]\n\t"
+#define TOMO_TERM_NONE(A) ""
+#define TOMO_TERM_BRICK(A) "ds_read_b32 %[l" A "], %[p" A "]\n\t"
+#define TOMO_LOAD_FLAT(X) "buffer_load_dword %[" X "], %[p0], %[rs], 0 offen\n\t"
+#define TOMO_LOAD_BRICK(X)                              \
+    "s_waitcnt lgkmcnt(0)\n\t"                          \
+    "v_add3_u32 %[l0], %[l0], %[l1], %[l2]\n\t"         \
+    "buffer_load_dword %[" X "], %[l0], %[rs], 0 offen\n\t"
+#define TOMO_WALK(MIN, LOAD, TERM, P0, P1, P2)                    \
+    "s_mov_b64 %[en], exec\n\t"                                   \
+    "s_mov_b64 %[sv], exec\n\t" TERM("0") TERM("1") TERM("2")     \
+    "\n.Ltomo_walk_%=:\n\t"                                       \
+    TOMO_STEP("0", "1", "ma", "mb", MIN, LOAD, TERM, P0, P1, P2)  \
+    TOMO_STEP("1", "2", "mb", "ma", MIN, LOAD, TERM, P0, P1, P2)  \
+    TOMO_STEP("2", "3", "ma", "mb", MIN, LOAD, TERM, P0, P1, P2)  \
+    TOMO_STEP("3", "0", "mb", "ma", MIN, LOAD, TERM, P0, P1, P2)  \
+    "s_sub_u32 %[cnt], %[cnt], 1\n\t"                             \
+    "s_cmp_lg_u32 %[cnt], 0\n\t"                                  \
+    "s_cbranch_scc1 .Ltomo_walk_%=\n\t"                           \
+    "s_branch .Ltomo_end_%=\n"                                    \
+    TOMO_EXIT("0", "2", "3") TOMO_EXIT("1", "3", "0")             \
+    TOMO_EXIT("2", "0", "1") TOMO_EXIT("3", "1", "2")             \
+    ".Ltomo_end_%=:\n\t"                                          \
+    "s_mov_b64 exec, %[en]\n\t"                                   \
+    "s_waitcnt vmcnt(0) lgkmcnt(0)"
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Words of a raw buffer resource over [base, base + bytes), uniform.
+__device__ inline u32x4 rsrc_words(const void *base, uint32_t bytes)
+{
+    const uint64_t b = (uint64_t)(uintptr_t)base;
+    u32x4 w;
+    w.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    w.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(b >> 32) & 0xffffu));
+    w.z = (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes);
+    w.w = 0x00020000u;
+    return w;
+}
+
+// ray_integrate over FP32 gathers at byte offset pos (kBrick false) or at the
+// sum of three LDS table entries at the addresses pos[0..2] (kBrick true).
+template <bool kObstacle, bool kBrick>
+__device__ inline double ray_integrate_buffer(RayState &r, int maxit, uint32_t (&pos)[3], const uint32_t (&st)[3],
+                                              u32x4 rs)
+{
+    double acc = 0.0, ma, mb = 0.0, cv, e0, e1 = 0.0, e2 = 0.0, e3 = 0.0;
+    float x0, x1 = 0.0f, x2 = 0.0f, x3 = 0.0f;
+    uint32_t l0, l1, l2, cnt = (uint32_t)(maxit + 3) >> 2;
+    uint64_t en, sv, tm;
+#define TOMO_ASM(MIN, LOAD, TERM, P0, P1, P2)                                                                       \
+    asm volatile(TOMO_WALK(MIN, LOAD, TERM, P0, P1, P2)                                                             \
+                 : [s0] "+&v"(r.s[0]), [s1] "+&v"(r.s[1]), [s2] "+&v"(r.s[2]), [p0] "+&v"(pos[0]),                  \
+                   [p1] "+&v"(pos[1]), [p2] "+&v"(pos[2]), [acc] "+&v"(acc), [e0] "=&v"(e0), [e1] "+&v"(e1),        \
+                   [e2] "+&v"(e2), [e3] "+&v"(e3), [x0] "=&v"(x0), [x1] "+&v"(x1), [x2] "+&v"(x2), [x3] "+&v"(x3),  \
+                   [ma] "=&v"(ma), [mb] "+&v"(mb), [cv] "=&v"(cv), [l0] "=&v"(l0), [l1] "=&v"(l1), [l2] "=&v"(l2),  \
+                   [cnt] "+&s"(cnt), [en] "=&s"(en), [sv] "=&s"(sv), [tm] "=&s"(tm)                                 \
+                 : [d0] "v"(r.ds[0]), [d1] "v"(r.ds[1]), [d2] "v"(r.ds[2]), [t0] "v"(st[0]), [t1] "v"(st[1]),       \
+                   [t2] "v"(st[2]), [send] "v"(r.send), [rs] "s"(rs)                                                \
+                 : "vcc", "scc", "memory")
+    if constexpr (kBrick) {
+        if constexpr (kObstacle) TOMO_ASM(TOMO_MIN_EXIT, TOMO_LOAD_BRICK, TOMO_TERM_BRICK, "p0", "p1", "p2");
+        else TOMO_ASM(TOMO_MIN_NONE, TOMO_LOAD_BRICK, TOMO_TERM_BRICK, "p0", "p1", "p2");
+    } else {
+        if constexpr (kObstacle) TOMO_ASM(TOMO_MIN_EXIT, TOMO_LOAD_FLAT, TOMO_TERM_NONE, "p0", "p0", "p0");
+        else TOMO_ASM(TOMO_MIN_NONE, TOMO_LOAD_FLAT, TOMO_TERM_NONE, "p0", "p0", "p0");
+    }
+#undef TOMO_ASM
+    return acc;
 }
 
 // Tile -> (view, pixel of this lane).  Views are sorted by tile_off.
@@ -303,6 +539,12 @@ __device__ inline LanePixel lane_pixel(const ViewDev *__restrict__ views, int nv
     if (log2_bw == 0) {  // 8x8 lanes at a 2-pixel pitch, wavefront w offset by (w&1, w>>1)
         lp.col = tx * kTile + (l & 7) * 2 + (w & 1);
         lp.row = ty * kTile + (l >> 3) * 2 + (w >> 1);
+        return lp;
+    }
+    if (log2_bw == 3) {
+        const int x = (l & 1) | ((l >> 1) & 2) | ((l >> 2) & 4), y = ((l >> 1) & 1) | ((l >> 2) & 2) | ((l >> 3) & 4);
+        lp.col = tx * kTile + (w & 1) * 8 + x;
+        lp.row = ty * kTile + (w >> 1) * 8 + y;
         return lp;
     }
     const int bw = 1 << log2_bw, bh = 64 >> log2_bw;
@@ -339,56 +581,34 @@ __device__ inline void project_tile(const GridDev &g, const ViewDev *__restrict_
         const bool wide = g.nvox >= ((int64_t)1 << 30);
         const uint32_t last = (uint32_t)(g.nvox - 1);
         const auto rc = make_rsrc(base, wide ? 0u : (uint32_t)(g.nvox * 4));
-        // software-pipelined by one segment: a step issues its voxel's gather
-        // before it adds the previous segment, so each load has a whole step
-        // to land
-        double acc = 0.0, dl_prev = 0.0;
-        float x_prev = 0.0f;
+        double acc;
+        const uint32_t unit = !kMapMask && g.nvox < ((int64_t)1 << 29) ? 4u : 1u;  // offsets in bytes where int32 holds them
+        uint32_t pos = (uint32_t)r.off * unit;
+        const uint32_t st[3] = {(uint32_t)r.st[0] * unit, (uint32_t)r.st[1] * unit, (uint32_t)r.st[2] * unit};
+        const auto plain = [](float x) { return (double)x; };
         if constexpr (kMapMask) {
             const auto rm = make_rsrc(map_mask, (uint32_t)g.nvox);
-            uint32_t m_prev = 0u;
-            auto walk_masked = [&](auto load) {
-                ray_walk(r, maxit, [&](int32_t off, double dl) {
-                    const float x = load((uint32_t)off);
-                    const uint32_t mk = buf_load_u8(rm, (uint32_t)off);
-                    acc = fma(dl_prev, m_prev ? (double)x_prev : 0.0, acc);
-                    x_prev = x;
-                    m_prev = mk;
-                    dl_prev = dl;
-                });
+            struct Masked {
+                float x;
+                uint32_t keep;
             };
+            const auto kept = [](const Masked &t) { return t.keep ? (double)t.x : 0.0; };
             if (wide)
-                walk_masked([&](uint32_t o) { return base[min(o, last)]; });
+                acc = ray_integrate<kObstacle>(
+                    r, maxit, pos, st, [&](uint32_t o) { return Masked{base[min(o, last)], buf_load_u8(rm, o)}; }, kept);
             else
-                walk_masked([&](uint32_t o) { return buf_load_f32(rc, o * 4u); });
-            if (!m_prev) x_prev = 0.0f;
+                acc = ray_integrate<kObstacle>(
+                    r, maxit, pos, st, [&](uint32_t o) { return Masked{buf_load_f32(rc, o * 4u), buf_load_u8(rm, o)}; },
+                    kept);
         } else if (wide) {
-            ray_walk(r, maxit, [&](int32_t off, double dl) {
-                const float x = base[min((uint32_t)off, last)];
-                acc = fma(dl_prev, (double)x_prev, acc);
-                x_prev = x;
-                dl_prev = dl;
-            });
-        } else if (g.nvox < ((int64_t)1 << 29)) {
-            // offsets in bytes from here on (below 2^31, so int32 holds them)
-            r.off *= 4;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) r.st[a] *= 4;
-            ray_walk(r, maxit, [&](int32_t off, double dl) {
-                const float x = buf_load_f32(rc, (uint32_t)off);
-                acc = fma(dl_prev, (double)x_prev, acc);
-                x_prev = x;
-                dl_prev = dl;
-            });
+            acc = ray_integrate<kObstacle>(r, maxit, pos, st, [&](uint32_t o) { return base[min(o, last)]; }, plain);
+        } else if (unit == 4u) {
+            uint32_t p3[3] = {pos, 0u, 0u};
+            acc = ray_integrate_buffer<kObstacle, false>(r, maxit, p3, st, rsrc_words(base, (uint32_t)(g.nvox * 4)));
         } else {
-            ray_walk(r, maxit, [&](int32_t off, double dl) {
-                const float x = buf_load_f32(rc, (uint32_t)off * 4u);
-                acc = fma(dl_prev, (double)x_prev, acc);
-                x_prev = x;
-                dl_prev = dl;
-            });
+            acc = ray_integrate<kObstacle>(r, maxit, pos, st, [&](uint32_t o) { return buf_load_f32(rc, o * 4u); },
+                                           plain);
         }
-        acc = fma(dl_prev, (double)x_prev, acc);
         out = (float)(acc * (r.dn * v.gain));
     }
     images[pix] = out;
@@ -439,39 +659,32 @@ __device__ inline void project_tile_bricked(const GridDev &g, const ViewDev *__r
         const float *__restrict__ base = bricked + (int64_t)v.frame * bk.frame_stride;
         const uint32_t last = (uint32_t)(bk.frame_stride - 1);
         const auto rc = make_rsrc(base, kWide ? 0u : (uint32_t)(bk.frame_stride * 4));
-        int i[3] = {ax.idx[0], ax.idx[1], ax.idx[2]};
-        int dir[3];
+        // positions per axis: the LDS address of the axis' offset term, or
+        // the voxel index without a table
+        uint32_t i[3], dir[3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) dir[a] = r.st[a] > 0 ? 1 : (r.st[a] < 0 ? -1 : 0);
-        // the kind of load is fixed per kernel (kWide: frames of 2^30 floats
-        // and more, which a buffer resource cannot span).  Pipelined by one
-        // segment: a step issues its voxel's gather before it adds the
-        // previous segment, so two gathers are in flight and each has a
-        // whole step to land
-        double acc = 0.0, dl_prev = 0.0, scur = 0.0;
-        float x_prev = 0.0f;
-        auto step = [&]() {
-            const double m = fmin(fmin(r.s[0], r.s[1]), fmin(r.s[2], r.send));
-            const uint32_t off = kLut ? lut[i[0]] + lut[g.n[0] + i[1]] + lut[g.n[0] + g.n[1] + i[2]]
-                                      : brick_offset(bk, i[0], i[1], i[2]);
-            const float x = kWide ? base[min(off, last)] : buf_load_f32(rc, kLut ? off : off * 4u);
-            const double dl = m - scur;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const bool t = (r.s[a] == m);
-                r.s[a] = fma(r.ds[a], tie_factor(t), r.s[a]);
-                i[a] += t ? dir[a] : 0;
-            }
-            scur = m;
-            acc = fma(dl_prev, (double)x_prev, acc);
-            x_prev = x;
-            dl_prev = dl;
-            return m >= r.send;
-        };
-        for (int it = 0; it < maxit; it += 4) {
-            if (step() || step() || step() || step()) break;
+        for (int a = 0; a < 3; ++a) {
+            const uint32_t one = kLut ? 4u : 1u;
+            const int tab0 = a == 0 ? 0 : (a == 1 ? g.n[0] : g.n[0] + g.n[1]);
+            i[a] = kLut ? lds_address(lut) + 4u * (uint32_t)(tab0 + ax.idx[a]) : (uint32_t)ax.idx[a];
+            dir[a] = r.st[a] > 0 ? one : (r.st[a] < 0 ? 0u - one : 0u);
         }
-        acc = fma(dl_prev, (double)x_prev, acc);
+        // the kind of load is fixed per kernel (kWide: frames of 2^30 floats
+        // and more, which a buffer resource cannot span)
+        double acc;
+        if constexpr (kLut && !kWide) {
+            acc = ray_integrate_buffer<kObstacle, true>(r, maxit, i, dir,
+                                                        rsrc_words(base, (uint32_t)(bk.frame_stride * 4)));
+        } else {
+            acc = ray_integrate<kObstacle>(
+                r, maxit, i, dir,
+                [&](const uint32_t (&p)[3]) {
+                    const uint32_t off = kLut ? lds_read_u32(p[0]) + lds_read_u32(p[1]) + lds_read_u32(p[2])
+                                              : brick_offset(bk, (int)p[0], (int)p[1], (int)p[2]);
+                    return kWide ? base[min(off, last)] : buf_load_f32(rc, off * 4u);
+                },
+                [](float x) { return (double)x; });
+        }
         out = (float)(acc * (r.dn * v.gain));
     }
     images[pix] = out;
