@@ -252,13 +252,6 @@ __device__ inline bool ray_table_get(const RayTable &t, int64_t i, RayState &r, 
     return r.send > 0.0;
 }
 
-// 1.0 if t else 0.0: only the high word differs, so one select; fma(ds, f,
-// s) then equals s + ds or s exactly.
-__device__ inline double tie_factor(bool t)
-{
-    return __builtin_bit_cast(double, (uint64_t)(t ? 0x3FF00000u : 0u) << 32);
-}
-
 // Advances every axis whose next crossing is m: s[a] += ds[a] and o += st[a]
 // where s[a] == m (exact on the common grid), the others left alone.  Written
 // under the execution mask (v_cmpx), three VALU instructions per axis, against
