@@ -28,8 +28,10 @@
 //   are rows 0 and 1 of one weight matrix, so the split costs nothing).
 // * Workgroups march through z by columns of the volume, so that a plane read
 //   once serves three planes of output.
-// * Weight gradients are reductions over all voxels: per-block FP64 partial
-//   sums, reduced in a fixed order (deterministic).
+// * Weight gradients are contractions over all voxels, on MFMA as well: BF16
+//   for the 16 -> 16 layer (FP64 beyond 64 voxels), FP64 where one factor is
+//   FP32.  Per-workgroup FP64 partial sums, reduced in a fixed order
+//   (deterministic for a device).
 #include <math.h>
 
 #include <map>
@@ -48,7 +50,7 @@ constexpr int kC = 16;
 constexpr int kTaps = 27;
 constexpr int OW1 = 0, OB1 = 432, OW2 = 448, OB2 = 7360, OW3 = 7376, OB3 = 7808;
 static_assert(OB3 + 1 == TOMO_CONVNET_NPARAMS, "parameter layout");
-constexpr int kWgBlocks = 512;  // blocks of the weight-gradient reductions
+constexpr int kWgBlocks = 512;  // most workgroups of the 16 -> 16 weight gradient (the workspace holds their sums)
 
 // round to nearest even (gfx950 converts in one instruction)
 __device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
@@ -59,14 +61,6 @@ struct Vol {
     int32_t nx, ny, nz;
     int64_t n;
 };
-
-__device__ inline void vox_ijk(const Vol &d, int64_t v, int &i, int &j, int &k)
-{
-    i = (int)(v % d.nx);
-    const int64_t r = v / d.nx;
-    j = (int)(r % d.ny);
-    k = (int)(r / d.ny);
-}
 
 // optional device scale sqrt(*norm2) (norm2 == nullptr: 1)
 __device__ inline float read_scale(const double *norm2)
@@ -383,20 +377,25 @@ __global__ __launch_bounds__(kThreads) void k_conv3(const bf16x8 *__restrict__ f
 // above and below: 1.27 reads per input voxel of a 16 x 16 column (plus two
 // planes per workgroup) against 2.53 for 16 x 4 x 4 tiles.
 
-// Workgroup b of a marching launch: its column (cx, cy) and planes [z0, z1).
+// A marching launch: `items` runs of at most cz planes in the columns.  One
+// workgroup per item, or (the weight gradients, whose per-workgroup sums have a
+// limited place) items taken in turn.
 struct March {
-    int32_t ncx, ncy, cz;  // columns along x and y, planes per workgroup
+    int32_t ncx, ncy, cz;  // columns along x and y, planes per item
+    int32_t items;
 };
 
-__device__ inline bool march_place(const March &m, const Vol &d, int &cx, int &cy, int &z0, int &z1)
+// First item of this workgroup: neighbouring items on one XCD.
+__device__ inline int march_first() { return (int)xcd_remap(blockIdx.x, gridDim.x); }
+
+// Item's column (cx, cy) and planes [z0, z1).
+__device__ inline void march_place(const March &m, const Vol &d, int item, int &cx, int &cy, int &z0, int &z1)
 {
-    const int b = (int)xcd_remap(blockIdx.x, gridDim.x);
-    cx = b % m.ncx;
-    const int r = b / m.ncx;
+    cx = item % m.ncx;
+    const int r = item / m.ncx;
     cy = r % m.ncy;
     z0 = (r / m.ncy) * m.cz;
     z1 = min(z0 + m.cz, d.nz);
-    return z0 < z1;
 }
 
 constexpr int kZX = 16, kZY = 16, kZR = kZX + 2;  // a column's outputs; rows and columns of its input plane
@@ -445,7 +444,7 @@ __global__ __launch_bounds__(kThreads) void k_conv16z(const uint16_t *__restrict
     __shared__ uint4 buf[4][2 * kZPlane];
     if (skip && *skip) return;
     int cx, cy, z0, z1;
-    if (!march_place(m, d, cx, cy, z0, z1)) return;
+    march_place(m, d, march_first(), cx, cy, z0, z1);
     const int x0 = cx * kZX, y0 = cy * kZY;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const auto rs = make_rsrc(in, (uint32_t)(d.n * kC * 2));
@@ -579,7 +578,7 @@ __global__ __launch_bounds__(kThreads) void k_conv1z(const bf16x8 *__restrict__ 
     __shared__ uint32_t xs[4][kZPlane];
     if (skip && *skip) return;
     int cx, cy, z0, z1;
-    if (!march_place(m, d, cx, cy, z0, z1)) return;
+    march_place(m, d, march_first(), cx, cy, z0, z1);
     const float s = read_scale(norm2);
     const float inv = s > 0.0f ? 1.0f / s : 0.0f;
     const int x0 = cx * kZX, y0 = cy * kZY;
@@ -694,151 +693,442 @@ __global__ __launch_bounds__(kThreads) void k_mse(const float *__restrict__ out,
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-// g_h2[v][c] = [a2[v][c] > 0] * sum_t w3[c][t] g[v - t + 1]  (data gradient of layer 3)
-__global__ __launch_bounds__(kThreads) void k_conv3_bwd(const float *__restrict__ P,
-                                                        const float *__restrict__ g,
-                                                        const uint16_t *__restrict__ a2, Vol d,
+// ---- marching training kernels: workgroups own columns of the volume over x
+// and y and walk z, with the planes they need in LDS rings (as the layers do).
+
+// Stages planes of a float field over a column of W x H voxels plus a one-voxel
+// rim into an LDS ring of four: load() reads plane z into registers (zero
+// outside the volume), put() stores it.
+template <int W, int H, int NT>
+struct FieldRing {
+    static constexpr int R = W + 2, N = R * (H + 2), kLoads = (N + NT - 1) / NT;
+    int64_t off[kLoads];  // in-plane offset of this thread's voxels (-1: outside)
+    __device__ void init(const Vol &d, int x0, int y0)
+    {
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            const int e = u * NT + threadIdx.x;
+            const int gx = x0 + e % R - 1, gy = y0 + e / R - 1;
+            off[u] = e < N && gx >= 0 && gx < d.nx && gy >= 0 && gy < d.ny ? (int64_t)gy * d.nx + gx : -1;
+        }
+    }
+    __device__ void load(const float *__restrict__ f, const Vol &d, int z, float (&v)[kLoads]) const
+    {
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            v[u] = 0.0f;
+            if (z >= 0 && z < d.nz && off[u] >= 0) v[u] = f[(int64_t)z * d.nx * d.ny + off[u]];
+        }
+    }
+    __device__ void put(float *plane, const float (&v)[kLoads]) const
+    {
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            const int e = u * NT + threadIdx.x;
+            if (e < N) plane[e] = v[u];
+        }
+    }
+};
+
+// g_h2[v][c] = [a2[v][c] > 0] * sum_t w3[c][t] g[v - t + 1]  (data gradient of
+// layer 3), FP32 sums over t in order.  Columns of 64 x 16: a thread takes four
+// rows at one x, so that a weight (a scalar register) serves four products and
+// each LDS value up to three rows.  Bound by its 432 FMAs per voxel (46 us at
+// one per lane and clock): 107 -> 55 us at 128^3 (one voxel per thread from
+// global memory before).  All 432 weights in registers at once spill (66 us from
+// LDS instead), and a store per dword rather than per 16 bytes takes 183 us.
+constexpr int kBX = 64, kBY = 16;
+__global__ __launch_bounds__(kThreads) void k_conv3_bwd(const float *__restrict__ P, const float *__restrict__ g,
+                                                        const uint16_t *__restrict__ a2, Vol d, March m,
                                                         uint16_t *__restrict__ gh2)
 {
-    for (int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x; v < d.n;
-         v += (int64_t)gridDim.x * kThreads) {
-        int i, j, k;
-        vox_ijk(d, v, i, j, k);
-        float gin[kTaps];
-#pragma unroll
-        for (int t = 0; t < kTaps; ++t) {  // output voxel v - (t - 1) used input v at tap t
-            const int ii = i - (t % 3 - 1), jj = j - ((t / 3) % 3 - 1), kk = k - (t / 9 - 1);
-            const bool ok = ii >= 0 && ii < d.nx && jj >= 0 && jj < d.ny && kk >= 0 && kk < d.nz;
-            gin[t] = ok ? g[((int64_t)kk * d.ny + jj) * d.nx + ii] : 0.0f;
-        }
-        const uint4 *ms = reinterpret_cast<const uint4 *>(a2 + v * kC);
-        const uint4 lo = ms[0], hi = ms[1];
-        const uint32_t mw[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        uint32_t packed[8];
-#pragma unroll
-        for (int c = 0; c < kC; c += 2) {
-            float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-            for (int t = 0; t < kTaps; ++t) {
-                s0 = fmaf(P[OW3 + c * kTaps + t], gin[t], s0);
-                s1 = fmaf(P[OW3 + (c + 1) * kTaps + t], gin[t], s1);
-            }
-            if (!(bf2f((uint16_t)(mw[c / 2] & 0xffffu)) > 0.f)) s0 = 0.f;
-            if (!(bf2f((uint16_t)(mw[c / 2] >> 16)) > 0.f)) s1 = 0.f;
-            packed[c / 2] = (uint32_t)f2bf(s0) | ((uint32_t)f2bf(s1) << 16);
-        }
-        uint4 *dst = reinterpret_cast<uint4 *>(gh2 + v * kC);
-        dst[0] = make_uint4(packed[0], packed[1], packed[2], packed[3]);
-        dst[1] = make_uint4(packed[4], packed[5], packed[6], packed[7]);
+    using Ring = FieldRing<kBX, kBY, kThreads>;
+    __shared__ float gs[4][Ring::N];
+    typedef const __attribute__((address_space(4))) float weight;  // scalar loads
+    weight *pw = reinterpret_cast<weight *>(reinterpret_cast<uintptr_t>(P + OW3));
+    int cx, cy, z0, z1;
+    march_place(m, d, march_first(), cx, cy, z0, z1);
+    const int x0 = cx * kBX, y0 = cy * kBY;
+    const int tx = threadIdx.x & 63, ty = 4 * (threadIdx.x >> 6);
+    const int xo = x0 + tx;
+    Ring ring;
+    ring.init(d, x0, y0);
+    float v[Ring::kLoads];
+    for (int k = -1; k <= 0; ++k) {
+        ring.load(g, d, z0 + k, v);
+        ring.put(gs[(z0 + k) & 3], v);
     }
-}
-
-// Per-block partial sums of the 16 -> 1 weight gradient and bias gradient:
-// gw3[c][t] = sum_v g[v] a2[v + t - 1][c]; gb3 = sum_v g[v].
-// Thread c*27 + t (of the first 432) owns one weight; thread 432 the bias.
-__global__ __launch_bounds__(448) void k_wgrad3(const float *__restrict__ g,
-                                                const uint16_t *__restrict__ a2, Vol d,
-                                                double *__restrict__ part /* [blocks][433] */)
-{
-    const int o = threadIdx.x;
-    const int c = o / kTaps, t = o % kTaps;
-    const int ox = t % 3 - 1, oy = (t / 3) % 3 - 1, oz = t / 9 - 1;
-    double acc = 0.0;
-    for (int64_t v = blockIdx.x; v < d.n; v += gridDim.x) {
-        const float gv = g[v];
-        if (o == 432) {
-            acc += gv;
-        } else if (o < 432) {
-            int i, j, k;
-            vox_ijk(d, v, i, j, k);
-            const int ii = i + ox, jj = j + oy, kk = k + oz;
-            if (ii >= 0 && ii < d.nx && jj >= 0 && jj < d.ny && kk >= 0 && kk < d.nz)
-                acc += (double)gv * bf2f(a2[(((int64_t)kk * d.ny + jj) * d.nx + ii) * kC + c]);
-        }
-    }
-    if (o < 433) part[(int64_t)blockIdx.x * 433 + o] = acc;
-}
-
-// Per-block partial sums of the 1 -> 16 weight gradient:
-// gw1[c][t] = sum_v gh1[v][c] x[v + t - 1] / s; gb1[c] = sum_v gh1[v][c].
-__global__ __launch_bounds__(448) void k_wgrad1(const uint16_t *__restrict__ gh1,
-                                                const float *__restrict__ x, Vol d,
-                                                double *__restrict__ part /* [blocks][448] */)
-{
-    const int o = threadIdx.x;
-    double acc = 0.0;
-    if (o < 432) {
-        const int c = o / kTaps, t = o % kTaps;
-        const int ox = t % 3 - 1, oy = (t / 3) % 3 - 1, oz = t / 9 - 1;
-        for (int64_t v = blockIdx.x; v < d.n; v += gridDim.x) {
-            int i, j, k;
-            vox_ijk(d, v, i, j, k);
-            const int ii = i + ox, jj = j + oy, kk = k + oz;
-            if (ii >= 0 && ii < d.nx && jj >= 0 && jj < d.ny && kk >= 0 && kk < d.nz)
-                acc += (double)bf2f(gh1[v * kC + c]) * x[((int64_t)kk * d.ny + jj) * d.nx + ii];
-        }
-    } else {
-        const int c = o - 432;
-        for (int64_t v = blockIdx.x; v < d.n; v += gridDim.x) acc += bf2f(gh1[v * kC + c]);
-    }
-    part[(int64_t)blockIdx.x * 448 + o] = acc;
-}
-
-// Per-block partial sums of the 16 -> 16 weight gradient:
-// gw2[co][ci][t] = sum_v gh2[v][co] a1[v + t - 1][ci]; gb2[co] = sum_v gh2[v][co].
-// Thread (co, ci) = (tid / 16, tid % 16) owns the 27 taps of one pair.
-__global__ __launch_bounds__(kThreads) void k_wgrad2(const uint16_t *__restrict__ gh2,
-                                                     const uint16_t *__restrict__ a1, Vol d,
-                                                     double *__restrict__ part /* [blocks][6928] */)
-{
-    const int co = threadIdx.x / 16, ci = threadIdx.x % 16;
-    float acc[kTaps];
+    ring.load(g, d, z0 + 1, v);
+    for (int z = z0; z < z1; ++z) {
+        ring.put(gs[(z + 1) & 3], v);
+        __syncthreads();
+        if (z + 1 < z1) ring.load(g, d, z + 2, v);
+        // gin[dz][y][dx] = g at (x + dx - 1, y - 1, z + dz - 1) of the thread's column
+        float gin[3][kTY + 2][3];
 #pragma unroll
-    for (int t = 0; t < kTaps; ++t) acc[t] = 0.f;
-    double bacc = 0.0;
-    double dacc[kTaps];
+        for (int dz = 0; dz < 3; ++dz)
 #pragma unroll
-    for (int t = 0; t < kTaps; ++t) dacc[t] = 0.0;
-    int cnt = 0;
-    const int64_t nrows = (int64_t)d.ny * d.nz;
-    for (int64_t row = blockIdx.x; row < nrows; row += gridDim.x) {
-        const int j = (int)(row % d.ny), k = (int)(row / d.ny);
-        for (int i = 0; i < d.nx; ++i) {
-            const int64_t v = (row * d.nx) + i;
-            const float gv = bf2f(gh2[v * kC + co]);
-            if (ci == 0) bacc += gv;
-            if (gv == 0.0f) continue;  // ReLU zeros: common, and they add nothing
+            for (int y = 0; y < kTY + 2; ++y)
 #pragma unroll
-            for (int t = 0; t < kTaps; ++t) {
-                const int ii = i + t % 3 - 1, jj = j + (t / 3) % 3 - 1, kk = k + t / 9 - 1;
-                if (ii >= 0 && ii < d.nx && jj >= 0 && jj < d.ny && kk >= 0 && kk < d.nz)
-                    acc[t] = fmaf(gv, bf2f(a1[(((int64_t)kk * d.ny + jj) * d.nx + ii) * kC + ci]), acc[t]);
-            }
-            if (++cnt == 64) {  // fold the FP32 partials into FP64 regularly
+                for (int dx = 0; dx < 3; ++dx)
+                    gin[dz][y][dx] = gs[(z - 1 + dz) & 3][(ty + y) * Ring::R + tx + dx];
+        // two channels at a time, in a loop of their own: 54 of the 432 weights
+        // fit the scalar registers (all at once were spilled: 107 us).  The mask
+        // and the results turn through four dwords, so that both move 16 bytes
+        const int64_t vo = ((int64_t)z * d.ny + y0 + ty) * d.nx + xo;
+        weight *pc = pw;
+        uint4 mk[kTY], res[kTY];
 #pragma unroll
-                for (int t = 0; t < kTaps; ++t) {
-                    dacc[t] += acc[t];
-                    acc[t] = 0.f;
+        for (int y = 0; y < kTY; ++y) mk[y] = res[y] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll 1
+        for (int i = 0; i < kC / 2; ++i, pc += 2 * kTaps) {
+            if ((i & 3) == 0) {
+#pragma unroll
+                for (int y = 0; y < kTY; ++y) {
+                    mk[y] = make_uint4(0u, 0u, 0u, 0u);
+                    if (xo < d.nx && y0 + ty + y < d.ny)
+                        mk[y] = reinterpret_cast<const uint4 *>(a2 + (vo + (int64_t)y * d.nx) * kC)[i >> 2];
                 }
-                cnt = 0;
+            }
+            float s0[kTY], s1[kTY];
+#pragma unroll
+            for (int y = 0; y < kTY; ++y) s0[y] = s1[y] = 0.f;
+#pragma unroll
+            for (int t = 0; t < kTaps; ++t) {  // output voxel v - (t - 1) used input v at tap t
+                const float w0 = pc[t], w1 = pc[kTaps + t];
+#pragma unroll
+                for (int y = 0; y < kTY; ++y) {
+                    const float gv = gin[2 - t / 9][y + 2 - (t / 3) % 3][2 - t % 3];
+                    s0[y] = fmaf(w0, gv, s0[y]);
+                    s1[y] = fmaf(w1, gv, s1[y]);
+                }
+            }
+#pragma unroll
+            for (int y = 0; y < kTY; ++y) {
+                const uint32_t lo = f2bf(bf2f((uint16_t)(mk[y].x & 0xffffu)) > 0.f ? s0[y] : 0.f);
+                const uint32_t hi = f2bf(bf2f((uint16_t)(mk[y].x >> 16)) > 0.f ? s1[y] : 0.f);
+                mk[y] = make_uint4(mk[y].y, mk[y].z, mk[y].w, 0u);
+                res[y] = make_uint4(res[y].y, res[y].z, res[y].w, lo | hi << 16);
+            }
+            if ((i & 3) == 3) {
+#pragma unroll
+                for (int y = 0; y < kTY; ++y)
+                    if (xo < d.nx && y0 + ty + y < d.ny)
+                        reinterpret_cast<uint4 *>(gh2 + (vo + (int64_t)y * d.nx) * kC)[i >> 2] = res[y];
             }
         }
     }
-    double *dst = part + (int64_t)blockIdx.x * 6928;
-#pragma unroll
-    for (int t = 0; t < kTaps; ++t) dst[(co * kC + ci) * kTaps + t] = dacc[t] + acc[t];
-    if (ci == 0) dst[6912 + co] = bacc;
 }
 
-// grad[off + o] = sum over blocks of part[b][o] (fixed order).
-__global__ void k_reduce_parts(const double *__restrict__ part, int nblocks, int width,
-                               float *__restrict__ grad, int off)
+// Weight gradients of the layers with one channel on one side, per-workgroup
+// partial sums in FP64 on v_mfma_f64_16x16x4_f64 (products of a BF16 and an
+// FP32 value are exact in FP64): D[c][t] += act[v][c] field[v + o_t], four
+// voxels per instruction, the 27 taps as the columns of two tiles.
+//   kFirst: gw1[c][t] = sum_v gh1[v][c] x[v + t - 1], gb1[c] = sum_v gh1[v][c]
+//     (the column after the taps: a field of ones); part rows of 448:
+//     [16][27] then [16].
+//   otherwise: gw3[c][t] = sum_u a2[u][c] g[u - (t - 1)] (the same sum over
+//     input voxels), gb3 = sum_v g[v]; part rows of 433: [16][27] then 1.
+// Lane l holds act[v + l / 16][l % 16], field[v + l / 16 + o_t] for t = l % 16
+// (and 16 + l % 16), and rows 4 r + l / 16, r = 0..3, of column l % 16 of the
+// result.  Columns of 16 x 16, a wavefront taking four rows of each plane.
+// Bound by the FP64 matrix rate (27 us of products at 128^3): 3435 -> 44 us
+// (first layer) and 2627 -> 44 us there (one thread per output element before).
+constexpr int kFPart1 = 448, kFPart3 = 433;
+constexpr int kFieldBlocks = 4096;  // most workgroups
+template <bool kFirst>
+__global__ __launch_bounds__(kThreads) void k_wgrad_field(const uint16_t *__restrict__ act,
+                                                          const float *__restrict__ field, Vol d, March m,
+                                                          double *__restrict__ part)
 {
-    const int o = blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= width) return;
+    typedef double f64x4 __attribute__((ext_vector_type(4)));
+    using Ring = FieldRing<kZX, kZY, kThreads>;
+    __shared__ float fs[4][Ring::N];
+    __shared__ uint4 as[2][kZX * kZY * 2];  // two planes of act: [voxel][16] BF16
+    __shared__ double red[kThreads / 64][8][64];
+    __shared__ double gsum[kThreads / 64];
+    constexpr int kWidth = kFirst ? kFPart1 : kFPart3;
+    double *dst = part + (int64_t)blockIdx.x * kWidth;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = lane % 16, k = lane / 16;
+    // word offsets of this lane's two taps for voxel (k, 4 wave) when plane
+    // z - 1 sits in ring slot ph
+    int off[4][2];
+    const int t1 = min(16 + n, kTaps - 1);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int tt = j == 0 ? n : t1, t = kFirst ? tt : kTaps - 1 - tt;
+#pragma unroll
+        for (int ph = 0; ph < 4; ++ph)
+            off[ph][j] = ((ph + t / 9) & 3) * Ring::N + (4 * wave + (t / 3) % 3) * Ring::R + k + t % 3;
+    }
+    const bool live1 = 16 + n < kTaps;                       // tile 1: taps 16..26,
+    const double rest = kFirst && 16 + n == kTaps ? 1.0 : 0.0;  // ones after them, then zeros
+    f64x4 acc[2][2];  // [voxel parity][tile]: independent products back to back
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f64x4{0., 0., 0., 0.};
+    double gb = 0.0;
+    const float *fw = &fs[0][0];
+    for (int it = march_first(); it < m.items; it += gridDim.x) {
+        int cx, cy, z0, z1;
+        march_place(m, d, it, cx, cy, z0, z1);
+        const int x0 = cx * kZX, y0 = cy * kZY;
+        Ring ring;
+        ring.init(d, x0, y0);
+        // act voxel of this thread: slots 2 v and 2 v + 1, v = threadIdx.x
+        const bool ain = x0 + (int)(threadIdx.x & 15) < d.nx && y0 + (int)(threadIdx.x >> 4) < d.ny;
+        const int64_t aoff = ((int64_t)(y0 + (threadIdx.x >> 4)) * d.nx + x0 + (threadIdx.x & 15)) * kC;
+        float v[Ring::kLoads];
+        uint4 av[2];
+        auto load_act = [&](int z) {
+            av[0] = av[1] = make_uint4(0u, 0u, 0u, 0u);
+            if (ain) {
+                const uint4 *p = reinterpret_cast<const uint4 *>(act + (int64_t)z * d.nx * d.ny * kC + aoff);
+                av[0] = p[0];
+                av[1] = p[1];
+            }
+        };
+        __syncthreads();  // the previous item's planes are done with
+        ring.load(field, d, z0 - 1, v);
+        ring.put(fs[0], v);
+        ring.load(field, d, z0, v);
+        ring.put(fs[1], v);
+        ring.load(field, d, z0 + 1, v);
+        load_act(z0);
+        auto step = [&](auto phase, int z) {
+            constexpr int ph = decltype(phase)::value;
+            ring.put(fs[(ph + 2) & 3], v);
+            as[ph & 1][2 * threadIdx.x] = av[0];
+            as[ph & 1][2 * threadIdx.x + 1] = av[1];
+            __syncthreads();
+            if (z + 1 < z1) {
+                ring.load(field, d, z + 2, v);
+                load_act(z + 1);
+            }
+            const uint16_t *ap = reinterpret_cast<const uint16_t *>(as[ph & 1]) + ((4 * wave * kZX + k) * kC + n);
+#pragma unroll
+            for (int y = 0; y < 4; ++y)
+#pragma unroll
+                for (int q = 0; q < kZX / 4; ++q) {
+                    const double a = (double)bf2f(ap[(y * kZX + 4 * q) * kC]);
+                    const double b0 = (double)fw[off[ph][0] + y * Ring::R + 4 * q];
+                    const double f1 = (double)fw[off[ph][1] + y * Ring::R + 4 * q];
+                    const double b1 = live1 ? f1 : rest;
+                    acc[q & 1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b0, acc[q & 1][0], 0, 0, 0);
+                    acc[q & 1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b1, acc[q & 1][1], 0, 0, 0);
+                }
+            if (!kFirst)  // this thread's own voxel (zero outside the volume)
+                gb += (double)fs[(ph + 1) & 3][((threadIdx.x >> 4) + 1) * Ring::R + (threadIdx.x & 15) + 1];
+        };
+        for (int z = z0;; z += 4) {
+            step(std::integral_constant<int, 0>{}, z);
+            if (z + 1 >= z1) break;
+            step(std::integral_constant<int, 1>{}, z + 1);
+            if (z + 2 >= z1) break;
+            step(std::integral_constant<int, 2>{}, z + 2);
+            if (z + 3 >= z1) break;
+            step(std::integral_constant<int, 3>{}, z + 3);
+            if (z + 4 >= z1) break;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave][4 * j + r][lane] = acc[0][j][r] + acc[1][j][r];
+    if (!kFirst) {
+        for (int o = 32; o > 0; o >>= 1) gb += __shfl_down(gb, o, 64);
+        if (lane == 0) gsum[wave] = gb;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 512; e += kThreads) {
+        const int q = e >> 6, l = e & 63;
+        const double sum = (red[0][q][l] + red[1][q][l]) + (red[2][q][l] + red[3][q][l]);
+        const int c = 4 * (q & 3) + l / 16, t = 16 * (q >> 2) + l % 16;
+        if (t < kTaps) dst[c * kTaps + t] = sum;
+        else if (kFirst && t == kTaps) dst[16 * kTaps + c] = sum;
+    }
+    if (!kFirst && threadIdx.x == 0) dst[16 * kTaps] = (gsum[0] + gsum[1]) + (gsum[2] + gsum[3]);
+}
+
+// Per-workgroup partial sums of the 16 -> 16 weight gradient on MFMA:
+// gw2[co][ci][t] = sum_v gh2[v][co] a1[v + t - 1][ci]; gb2[co] = sum_v gh2[v][co].
+// The contraction runs over voxels, 32 along x per v_mfma_f32_16x16x32_bf16
+// (BF16 products are exact in FP32), so both operands are staged with voxels
+// along a lane's elements: LDS rows [channel][x].  Columns of 32 x 8; nine
+// wavefronts, one per x-triple of taps, each over the plane's eight rows: its
+// three sums are FP32 over two instructions (64 voxels) and FP64 beyond.  A
+// tap's shift along x is taken in registers from the five dwords around the
+// lane's eight voxels (dx = 1: a 16-bit funnel shift).  The bias sums in FP64
+// throughout, a row per wavefront.  Bound by VALU (the FP64 folds) and LDS
+// reads, about 18 us each, next to 12 us of products at 128^3, and by one
+// workgroup per CU (134 registers; held to 96 for two, 35 spill): 9650 -> 69
+// us there (one thread per output over FP64 products before).
+constexpr int kWX = 32, kWY = 8, kWThreads = 576, kWPart = 6928;
+constexpr int kWRow = 20;                           // dwords per [channel] row: 36 voxels, padded off the banks
+constexpr int kWA1 = (kWY + 2) * kC * kWRow;        // dwords of an a1 plane: [row][channel][x + 1]
+constexpr int kWGh = kWY * kC * kWRow;              // dwords of a gh2 plane: [row][channel][x]
+static_assert(kWThreads == kTriples * 64 && kWY <= kTriples, "a wavefront per x-triple, a bias row per wavefront");
+__global__ __launch_bounds__(kWThreads) void k_wgrad2(const uint16_t *__restrict__ gh2,
+                                                      const uint16_t *__restrict__ a1, Vol d, March m,
+                                                      double *__restrict__ part)
+{
+    __shared__ __align__(16) uint32_t sa[4][kWA1];
+    __shared__ __align__(16) uint32_t sg[2][kWGh];
+    __shared__ double bred[kWY][64];
+    double *dst = part + (int64_t)blockIdx.x * kWPart;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int dz = wave / 3, dy = wave % 3;
+    const int n = lane % 16, g = lane / 16;
+    // staging: a share is a pair of x neighbours and half of their channels,
+    // two 16-byte loads transposed into eight dwords (one per channel)
+    constexpr int kSharesA = (kWY + 2) * (kWX / 2 + 1) * 2;  // pairs x = -1 .. 32
+    constexpr int kSharesG = kWY * (kWX / 2) * 2;            // taken by the last threads
+    static_assert(kSharesA <= kWThreads && kSharesG <= kWThreads, "one share per thread");
+    struct Share {
+        int64_t off;   // of the pair's first voxel in a plane, in elements
+        bool in0, in1; // voxels inside the volume
+        int lds;       // dword of channel 0 of the half
+    };
+    auto share = [&](int i, int pairs, int rim, int x0, int y0) {
+        Share t;
+        const int h = i & 1, r = i >> 1, px = r % pairs, row = r / pairs;
+        const int gx = x0 + 2 * px - rim, gy = y0 + row - rim;
+        const bool yin = gy >= 0 && gy < d.ny;
+        t.in0 = yin && gx >= 0 && gx < d.nx;
+        t.in1 = yin && gx + 1 >= 0 && gx + 1 < d.nx;
+        t.off = ((int64_t)gy * d.nx + gx) * kC + 8 * h;
+        t.lds = (row * kC + 8 * h) * kWRow + px;
+        return t;
+    };
+    const int64_t plane = (int64_t)d.nx * d.ny * kC;
+    auto load = [&](const uint16_t *src, const Share &t, int z, uint4 (&v)[2]) {
+        v[0] = v[1] = make_uint4(0u, 0u, 0u, 0u);
+        if (z < 0 || z >= d.nz) return;
+        if (t.in0) v[0] = *reinterpret_cast<const uint4 *>(src + z * plane + t.off);
+        if (t.in1) v[1] = *reinterpret_cast<const uint4 *>(src + z * plane + t.off + kC);
+    };
+    auto put = [&](uint32_t *dst_, const Share &t, const uint4 (&v)[2]) {
+        const uint32_t lo[4] = {v[0].x, v[0].y, v[0].z, v[0].w}, hi[4] = {v[1].x, v[1].y, v[1].z, v[1].w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            dst_[t.lds + (2 * c) * kWRow] = __builtin_amdgcn_perm(hi[c], lo[c], 0x05040100u);
+            dst_[t.lds + (2 * c + 1) * kWRow] = __builtin_amdgcn_perm(hi[c], lo[c], 0x07060302u);
+        }
+    };
+    const bool has_a = (int)threadIdx.x < kSharesA, has_g = (int)threadIdx.x >= kWThreads - kSharesG;
+    double dacc[3][4];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dacc[t][r] = 0.0;
+    double bacc = 0.0;
+    for (int it = march_first(); it < m.items; it += gridDim.x) {
+        int cx, cy, z0, z1;
+        march_place(m, d, it, cx, cy, z0, z1);
+        Share ia = share(has_a ? (int)threadIdx.x : 0, kWX / 2 + 1, 1, cx * kWX, cy * kWY);
+        Share ig = share(has_g ? (int)threadIdx.x - (kWThreads - kSharesG) : 0, kWX / 2, 0, cx * kWX, cy * kWY);
+        ia.in0 = ia.in0 && has_a;
+        ia.in1 = ia.in1 && has_a;
+        ig.in0 = ig.in0 && has_g;
+        ig.in1 = ig.in1 && has_g;
+        uint4 va[2], vg[2];
+        __syncthreads();  // the previous item's planes are done with
+        for (int q = -1; q <= 0; ++q) {
+            load(a1, ia, z0 + q, va);
+            if (has_a) put(sa[(z0 + q) & 3], ia, va);
+        }
+        load(a1, ia, z0 + 1, va);
+        load(gh2, ig, z0, vg);
+        for (int z = z0; z < z1; ++z) {
+            if (has_a) put(sa[(z + 1) & 3], ia, va);
+            if (has_g) put(sg[z & 1], ig, vg);
+            __syncthreads();
+            if (z + 1 < z1) {
+                load(a1, ia, z + 2, va);
+                load(gh2, ig, z + 1, vg);
+            }
+            const uint32_t *pa = sa[(z - 1 + dz) & 3] + (dy * kC + n) * kWRow + 4 * g;
+            const uint32_t *pg = sg[z & 1] + n * kWRow + 4 * g;
+#pragma unroll
+            for (int yp = 0; yp < kWY; yp += 4) {  // two pairs of rows, a sum each
+                f32x4 acc[2][3];
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) acc[p][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        const int y = yp + 2 * p + i;
+                        const uint4 q = *reinterpret_cast<const uint4 *>(pg + y * kC * kWRow);
+                        const bf16x8 av = __builtin_bit_cast(bf16x8, q);
+                        if (y == wave) {
+                            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                bacc += (double)bf2f((uint16_t)(w[e] & 0xffffu)) + (double)bf2f((uint16_t)(w[e] >> 16));
+                        }
+                        const uint4 u = *reinterpret_cast<const uint4 *>(pa + y * kC * kWRow);
+                        const uint32_t w[5] = {u.x, u.y, u.z, u.w, pa[y * kC * kWRow + 4]};
+#pragma unroll
+                        for (int dx = 0; dx < 3; ++dx) {
+                            uint32_t s4[4];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                s4[e] = dx == 0 ? w[e]
+                                                : (dx == 1 ? __builtin_amdgcn_alignbit(w[e + 1], w[e], 16) : w[e + 1]);
+                            acc[p][dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, s4),
+                                                                                acc[p][dx], 0, 0, 0);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);  // five products between two of one sum
+                }
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) dacc[t][r] += (double)acc[p][t][r];
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dst[((4 * g + r) * kC + n) * kTaps + 3 * wave + t] = dacc[t][r];
+    if (wave < kWY) bred[wave][lane] = bacc;
+    __syncthreads();
+    if (threadIdx.x < kC) {
+        double b = 0.0;
+        for (int w = 0; w < kWY; ++w)
+            for (int q = 0; q < 4; ++q) b += bred[w][16 * q + threadIdx.x];
+        dst[kC * kC * kTaps + threadIdx.x] = b;
+    }
+}
+
+// grad[off + o] = sum over blocks of part[b][o], in a fixed order: eight
+// threads per output take the blocks b = k, k + 8, ... and are added in turn.
+constexpr int kRedOut = 32;
+__global__ __launch_bounds__(kThreads) void k_reduce_parts(const double *__restrict__ part, int nblocks, int width,
+                                                           float *__restrict__ grad, int off)
+{
+    static_assert(kThreads == 8 * kRedOut, "eight threads per output");
+    __shared__ double red[8][kRedOut];
+    const int l = threadIdx.x % kRedOut, k = threadIdx.x / kRedOut, o = blockIdx.x * kRedOut + l;
     double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += part[(int64_t)b * width + o];
-    grad[off + o] = (float)s;
+    if (o < width) {
+#pragma unroll 8
+        for (int b = k; b < nblocks; b += 8) s += part[(int64_t)b * width + o];
+    }
+    red[k][l] = s;
+    __syncthreads();
+    if (k == 0 && o < width) {
+        for (int q = 1; q < 8; ++q) s += red[q][l];
+        grad[off + o] = (float)s;
+    }
 }
 
 __global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
@@ -865,6 +1155,7 @@ struct NetWs {
     double *loss_part;       // [kRedLossBlocks]
 };
 constexpr int kLossBlocks = 1024;
+static_assert((int64_t)kFieldBlocks * kFPart1 <= (int64_t)kWgBlocks * kWPart, "the partial sums' place");
 
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -884,7 +1175,7 @@ static size_t ws_layout(int64_t n, NetWs *w, char *base)
     t.g = (float *)take(sizeof(float) * n);
     t.frag = (bf16x8 *)take(sizeof(bf16x8) * kFragFwd);
     t.fragT = (bf16x8 *)take(sizeof(bf16x8) * kFragConv);
-    t.part = (double *)take(sizeof(double) * kWgBlocks * 6928);
+    t.part = (double *)take(sizeof(double) * kWgBlocks * kWPart);
     t.loss_part = (double *)take(sizeof(double) * kLossBlocks);
     if (w) *w = t;
     return off;
@@ -902,10 +1193,12 @@ static dim3 tile_grid(const Vol &d)
                 (unsigned)((d.nz + kTZ - 1) / kTZ));
 }
 
-// Launch of a marching kernel over columns of cx x cy outputs: as many planes
-// per workgroup as leave about one round of the workgroups that stay resident
-// on the device (occupancy x compute units, queried once per kernel).
-static unsigned march_grid(const void *kernel, const Vol &d, int cx, int cy, March &m)
+// Launch of a marching kernel of nt lanes over columns of cx x cy outputs: as
+// many planes per item as leave about one round of the workgroups that stay
+// resident on the device (occupancy x compute units, queried once per kernel);
+// one workgroup per item, or at most `most` that take the items in turn.
+static unsigned march_grid(const void *kernel, const Vol &d, int cx, int cy, March &m, int64_t most = 0,
+                           int nt = kThreads)
 {
     static std::mutex mu;
     static std::map<const void *, int64_t> resident;
@@ -919,18 +1212,20 @@ static unsigned march_grid(const void *kernel, const Vol &d, int cx, int cy, Mar
             int dev = 0, cus = 0, per = 0;
             (void)hipGetDevice(&dev);
             (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-            (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, kThreads, 0);
+            (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, nt, 0);
             r = (int64_t)(cus > 0 ? cus : 256) * (per > 0 ? per : 1);
             resident[kernel] = r;
         }
     }
+    if (most > 0 && r > most) r = most;
     m.ncx = (d.nx + cx - 1) / cx;
     m.ncy = (d.ny + cy - 1) / cy;
     const int64_t cols = (int64_t)m.ncx * m.ncy;
     int64_t chunks = r / cols;
     chunks = chunks < 1 ? 1 : (chunks > d.nz ? d.nz : chunks);
     m.cz = (int32_t)((d.nz + chunks - 1) / chunks);
-    return (unsigned)(cols * ((d.nz + m.cz - 1) / m.cz));
+    m.items = (int32_t)(cols * ((d.nz + m.cz - 1) / m.cz));
+    return (unsigned)(most > 0 && m.items > most ? most : m.items);
 }
 
 // The layers on a stored activation: the marching kernels, or one tile per
@@ -969,12 +1264,6 @@ static void launch_conv3(const bf16x8 *frag3, const float *P, const uint16_t *a2
     } else {
         hipLaunchKernelGGL(k_conv3, tile_grid(d), dim3(kThreads), 0, s, frag3, P, a2, d, norm2, map_mask, out, skip);
     }
-}
-
-static unsigned vox_blocks(int64_t n)
-{
-    int64_t b = (n + kThreads - 1) / kThreads;
-    return (unsigned)(b > 8192 ? 8192 : (b < 1 ? 1 : b));
 }
 
 // z = s N(x / s) on the device (s = sqrt(*norm2), or 1), zero where the map
@@ -1056,19 +1345,28 @@ static int convnet_train_pass(const tomo_cube *cube, const float *params_d, cons
                            w.loss_part);
         g_d = w.g;
     }
+    March m;
+    unsigned nb;
+    auto reduce = [&](unsigned blocks, int width, int off) {
+        hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)((width + kRedOut - 1) / kRedOut)), dim3(kThreads), 0, s, w.part,
+                           (int)blocks, width, grad_d, off);
+    };
     // layer 3
-    hipLaunchKernelGGL(k_wgrad3, dim3(kWgBlocks), dim3(448), 0, s, g_d, w.a2, d, w.part);
-    hipLaunchKernelGGL(k_reduce_parts, dim3(2), dim3(256), 0, s, w.part, kWgBlocks, 433, grad_d, OW3);
-    hipLaunchKernelGGL(k_conv3_bwd, dim3(vox_blocks(n)), dim3(kThreads), 0, s, params_d, g_d, w.a2, d, w.gh);
+    nb = march_grid(reinterpret_cast<const void *>(k_wgrad_field<false>), d, kZX, kZY, m, kFieldBlocks);
+    hipLaunchKernelGGL(k_wgrad_field<false>, dim3(nb), dim3(kThreads), 0, s, w.a2, g_d, d, m, w.part);
+    reduce(nb, kFPart3, OW3);
+    nb = march_grid(reinterpret_cast<const void *>(k_conv3_bwd), d, kBX, kBY, m);
+    hipLaunchKernelGGL(k_conv3_bwd, dim3(nb), dim3(kThreads), 0, s, params_d, g_d, w.a2, d, m, w.gh);
     // layer 2 (gh = d loss / d h2)
-    hipLaunchKernelGGL(k_wgrad2, dim3(kWgBlocks), dim3(kThreads), 0, s, w.gh, w.a1, d, w.part);
-    hipLaunchKernelGGL(k_reduce_parts, dim3((6928 + 255) / 256), dim3(256), 0, s, w.part, kWgBlocks, 6928,
-                       grad_d, OW2);
+    nb = march_grid(reinterpret_cast<const void *>(k_wgrad2), d, kWX, kWY, m, kWgBlocks, kWThreads);
+    hipLaunchKernelGGL(k_wgrad2, dim3(nb), dim3(kWThreads), 0, s, w.gh, w.a1, d, m, w.part);
+    reduce(nb, kWPart, OW2);
     // d loss / d h1 = [a1 > 0] conv^T(gh); written over a2 (no longer needed)
     launch_conv16<kMasked>(w.gh, w.fragT, nullptr, d, w.a1, w.a2, noskip, s);
     // layer 1
-    hipLaunchKernelGGL(k_wgrad1, dim3(kWgBlocks), dim3(448), 0, s, w.a2, x_d, d, w.part);
-    hipLaunchKernelGGL(k_reduce_parts, dim3(2), dim3(256), 0, s, w.part, kWgBlocks, 448, grad_d, OW1);
+    nb = march_grid(reinterpret_cast<const void *>(k_wgrad_field<true>), d, kZX, kZY, m, kFieldBlocks);
+    hipLaunchKernelGGL(k_wgrad_field<true>, dim3(nb), dim3(kThreads), 0, s, w.a2, x_d, d, m, w.part);
+    reduce(nb, kFPart1, OW1);
     return hip_fail(hipGetLastError(), "convnet backward launch");
 }
 
