@@ -11,16 +11,70 @@ constexpr int kYmaxParts = 64;  // partial maxima per view (64 workgroups per vi
 // Atomic adds at an LDS byte address: a walk that carries its bin as an
 // address needs no shift or base add per step (the clamp's result is the
 // instruction's address).
-__device__ inline void lds_add_u64(uint32_t a, unsigned long long v)
-{
-    __hip_atomic_fetch_add((__attribute__((address_space(3))) unsigned long long *)(uintptr_t)a, v,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
 __device__ inline void lds_add_f32(uint32_t a, float v)
 {
     __hip_atomic_fetch_add((__attribute__((address_space(3))) float *)(uintptr_t)a, v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+
+// One step of the walk through a block: the event's parameter M (the previous
+// one's in MP), the segment's fixed-point length added to its bin; lanes whose
+// event is the block's end leave the execution mask.
+#define TOMO_DEPOSIT_STEP(M, MP, MIN, K)                               \
+    "v_min_f64 %[" M "], %[s0], %[s1]\n\t"                             \
+    "v_min_f64 %[" M "], %[" M "], %[s2]\n\t" MIN(M)                   \
+    "v_add_f64 v[62:63], %[" M "], -%[" MP "]\n\t"                     \
+    "v_fma_f64 v[62:63], v[62:63], %[wys], %[one]\n\t"                 \
+    "v_min_u32_e32 %[b], %[lim], %[la]\n\t"                            \
+    "v_add_u32_e32 v63, 0xbcc80000, v63\n\t"                           \
+    "ds_add_u64 %[b], v[62:63]\n\t"                                    \
+    "v_cmpx_lt_f64_e32 vcc, %[" M "], %[send]\n\t"                     \
+    "s_cbranch_execz .Ltomo_end_%=\n\t"                                \
+    "s_mov_b64 %[sv], exec\n\t"                                        \
+    TOMO_AXIS("0", "la", M, TOMO_TERM_NONE) TOMO_AXIS("1", "la", M, TOMO_TERM_NONE) \
+    TOMO_AXIS_RARE("2", "la", M, TOMO_TERM_NONE, K)
+
+// Deposits the segments of the ray's walk from parameter E to X, in units of
+// wys, in the 64-bit LDS bins from address la on (la steps by st; lim is the
+// dummy bin).  A segment's product plus 1.5 * 2^52 rounds to an integer (below
+// 2^50 in magnitude) in the low mantissa bits; the high word of the sum's
+// exponent and leading bits, 0x43380000, is taken off again.  One machine loop
+// of sixteen VALU instructions a step: the compiler's form of the same loop
+// quiets the three crossings before each minimum (19 instructions) and keeps
+// the four exits of a body apart.  128^3 under 28 x 512^2, no table: 1.240 ms
+// with the axes updated by selects, 1.156 updated under the mask, 1.132 here;
+// a 256^3 x 8 batch under 60 x 512^2, from tables: 5.49 -> 5.20 ms.  The
+// deposits may still be under way at the end: deposits_done() before other
+// wavefronts read the bins.
+template <bool kObstacle>
+__device__ inline void deposit_walk(RayState &r, int maxit, double E, double X, double wys, uint32_t la,
+                                    const uint32_t (&st)[3], uint32_t lim)
+{
+    const double one = 6755399441055744.0;
+    double ma, mb = E;
+    uint32_t b, cnt = (uint32_t)(maxit + 3) >> 2;
+    uint64_t en, sv;
+#define TOMO_ASM(MIN)                                                                                             \
+    asm volatile("s_mov_b64 %[en], exec\n"                                                                        \
+                 ".Ltomo_walk_%=:\n\t" TOMO_DEPOSIT_STEP("ma", "mb", MIN, "0")                                    \
+                 TOMO_DEPOSIT_STEP("mb", "ma", MIN, "1") TOMO_DEPOSIT_STEP("ma", "mb", MIN, "2")                  \
+                 TOMO_DEPOSIT_STEP("mb", "ma", MIN, "3")                                                          \
+                 "s_sub_u32 %[cnt], %[cnt], 1\n\t"                                                                \
+                 "s_cmp_lg_u32 %[cnt], 0\n\t"                                                                     \
+                 "s_cbranch_scc1 .Ltomo_walk_%=\n"                                                                \
+                 ".Ltomo_end_%=:\n\t"                                                                             \
+                 "s_mov_b64 exec, %[en]"                                                                          \
+                 : [s0] "+&v"(r.s[0]), [s1] "+&v"(r.s[1]), [s2] "+&v"(r.s[2]), [la] "+&v"(la), [ma] "=&v"(ma),    \
+                   [mb] "+&v"(mb), [b] "=&v"(b), [cnt] "+&s"(cnt), [en] "=&s"(en), [sv] "=&s"(sv)   \
+                 : [d0] "v"(r.ds[0]), [d1] "v"(r.ds[1]), [d2] "v"(r.ds[2]), [t0] "v"(st[0]), [t1] "v"(st[1]),     \
+                   [t2] "v"(st[2]), [send] "v"(X), [wys] "v"(wys), [one] "s"(one),              \
+                   [lim] "s"(lim)                                                                                 \
+                 : "vcc", "scc", "v62", "v63", "memory")
+    if constexpr (kObstacle) TOMO_ASM(TOMO_MIN_EXIT);
+    else TOMO_ASM(TOMO_MIN_NONE);
+#undef TOMO_ASM
+}
+__device__ inline void deposits_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // max |gain y| over the share `part` of view v's unmasked pixels, as an
 // FP32 bit pattern (bit patterns of magnitudes order like the magnitudes;
@@ -510,38 +564,24 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
             }
             const double wys = (double)yv * r.dn * v.vscale;
             uint32_t la = bbase + 8u * (uint32_t)loc;  // the bin's LDS address
-            // sixteen VALU instructions a step (22 with the axes updated by
-            // selects): 128^3 under 28 x 512^2, no table, 1.240 -> 1.156 ms.
-            // Four steps per loop body, as in ray_walk; the clamp to the
-            // dummy bin only guards the LDS range (an address below the bins,
-            // which an exact walk never reaches, would stay inside the
-            // workgroup's LDS)
-            auto walk = [&](auto deposit) {
+            // the clamp to the dummy bin only guards the LDS range (an address
+            // below the bins, which an exact walk never reaches, would stay
+            // inside the workgroup's LDS)
+            if (finite) {
+                deposit_walk<kObstacle>(r, bd.maxit, E, X, wys, la, lst, blim);
+            } else {
                 double scur = E;
-                auto step = [&]() {
+                for (int it = 0; it < bd.maxit; ++it) {
                     const double m = next_event<kObstacle>(r.s, r.send);
-                    deposit(min(la, blim), (m - scur) * wys);
-                    if (m >= X) return true;
+                    lds_add_f32(min(la, blim), (float)((m - scur) * wys));
+                    if (m >= X) break;
                     advance(r.s, r.ds, m, la, lst);
                     scur = m;
-                    return false;
-                };
-                for (int it = 0; it < bd.maxit; it += 4) {
-                    if (step() || step() || step() || step()) break;
                 }
-            };
-            if (finite) {
-                walk([&](uint32_t l, double val) {
-                    // val + 1.5 * 2^52 rounds val to an integer (|val| < 2^50) in the low bits
-                    const double t = val + 6755399441055744.0;
-                    const long long q = (long long)__builtin_bit_cast(uint64_t, t) - 0x4338000000000000ll;
-                    lds_add_u64(l, (unsigned long long)q);
-                });
-            } else {
-                walk([&](uint32_t l, double val) { lds_add_f32(l, (float)val); });
             }
         }
     }
+    deposits_done();
     if (spills) atomicAdd(spill, spills);
     __syncthreads();
 
