@@ -20,7 +20,7 @@
 //   fills about 60% of its rectangle, and every ray dropped saves a set-up.
 //   Where footprints are a few pixels, intervals cannot save a pass, and the
 //   kernel compiled without them keeps 91 VGPRs against 128.
-// * The footprint is walked 256 pixels per pass in row-major order; each
+// * The footprint is walked in runs of 64 pixels in row-major order; each
 //   lane takes one of those rays, sets it up exactly as P does and walks
 //   only its part inside the block.  The walk's crossing parameters
 //   live on a power-of-two grid on which every sum the walk forms is exact:
