@@ -67,6 +67,7 @@ struct tomo_batch_s {
     unsigned grid_p = 0, grid_b = 0;
     bool rows = false;  // P^T walks footprint row intervals (most systems' plans ask for them)
     int32_t nt = 256;   // lanes per workgroup of the persistent P^T (the dominant system's tuning)
+    tomo::Rays rays = tomo::Rays::computed;  // where P^T takes the rays' set-up from
     uint16_t *kept = nullptr;  // kept-pixel rows of the systems' data masks
     float *bricks = nullptr;   // bricked copies of the cubes of the systems that walk bricks in P
     char *tables = nullptr;    // ray tables of the systems whose tuning asks for one

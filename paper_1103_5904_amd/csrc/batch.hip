@@ -32,6 +32,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "batch.h"
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(kThreads) void k_batch_absmax(const SysDev *__restr
     if (threadIdx.x == 0) ymax[blockIdx.x] = m;
 }
 
-template <int NT, bool kRows>
+template <int NT, bool kRows, Rays kRays>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_batch_backproject(
     const SysDev *__restrict__ sys, int32_t nsys, Operands ops, int64_t nitems, const uint32_t *__restrict__ ymax,
     unsigned long long *q, unsigned *__restrict__ spill)
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         const bool mm = ops.map && sd.map_mask, dm = sd.data_mask != nullptr;
         const KeptRows kept{sd.kept_pre, sd.kept_cols};
 #define TOMO_ITEM(M, D, O)                                                                                      \
-    blocked_item<NT, M, D, O, kRows>(sd.grid, sd.views, sd.frame_views, sd.frame_voff, sd.bd, li, ops.src[k],  \
+    blocked_item<NT, M, D, O, kRows, kRays>(sd.grid, sd.views, sd.frame_views, sd.frame_voff, sd.bd, li, ops.src[k],  \
                                      sd.map_mask, sd.data_mask, kept, ym, out, ops.acc, spill, sd.tab, bins, sh)
         if (sd.grid.has_sph) {  // the obstacle's variant: one code path for every mask combination
             if (mm && dm) TOMO_ITEM(true, true, true);
@@ -219,19 +220,22 @@ int batch_project_ops(tomo_batch b, const Operands &h, hipStream_t s)
     return TOMO_OK;
 }
 
-// The persistent P^T kernel for a batch's workgroup size and row mode.
+// The persistent P^T kernel for a batch's workgroup size, row mode and source
+// of the rays' set-up.
 template <int NT, bool kRows>
-static const void *batch_bp_kernel()
+static const void *batch_bp_kernel(Rays rays)
 {
-    return reinterpret_cast<const void *>(k_batch_backproject<NT, kRows>);
+    if (rays == Rays::table) return reinterpret_cast<const void *>(k_batch_backproject<NT, kRows, Rays::table>);
+    if (rays == Rays::either) return reinterpret_cast<const void *>(k_batch_backproject<NT, kRows, Rays::either>);
+    return reinterpret_cast<const void *>(k_batch_backproject<NT, kRows, Rays::computed>);
 }
 
-static const void *batch_bp_kernel_for(int nt, bool rows)
+static const void *batch_bp_kernel_for(int nt, bool rows, Rays rays)
 {
     switch (nt) {
-    case 512: return rows ? batch_bp_kernel<512, true>() : batch_bp_kernel<512, false>();
-    case 1024: return rows ? batch_bp_kernel<1024, true>() : batch_bp_kernel<1024, false>();
-    default: return rows ? batch_bp_kernel<256, true>() : batch_bp_kernel<256, false>();
+    case 512: return rows ? batch_bp_kernel<512, true>(rays) : batch_bp_kernel<512, false>(rays);
+    case 1024: return rows ? batch_bp_kernel<1024, true>(rays) : batch_bp_kernel<1024, false>(rays);
+    default: return rows ? batch_bp_kernel<256, true>(rays) : batch_bp_kernel<256, false>(rays);
     }
 }
 
@@ -246,20 +250,12 @@ int batch_backproject_ops(tomo_batch b, const Operands &ops, hipStream_t s)
                                         sd.kept_cols, s, ops.done[k]);
         if (rc) return rc;
     }
-#define TOMO_BATCH_BP(NT, R)                                                                                     \
-    hipLaunchKernelGGL((k_batch_backproject<NT, R>), dim3(b->grid_b), dim3(NT), b->lds_bytes, s, b->sys_d, b->nsys, \
-                       ops, b->nitems, b->ymax, b->q, b->spill)
-    if (b->nt == 512) {
-        if (b->rows) TOMO_BATCH_BP(512, true);
-        else TOMO_BATCH_BP(512, false);
-    } else if (b->nt == 1024) {
-        if (b->rows) TOMO_BATCH_BP(1024, true);
-        else TOMO_BATCH_BP(1024, false);
-    } else {
-        if (b->rows) TOMO_BATCH_BP(256, true);
-        else TOMO_BATCH_BP(256, false);
-    }
-#undef TOMO_BATCH_BP
+    Operands arg_ops = ops;
+    void *args[] = {&b->sys_d, &b->nsys, &arg_ops, &b->nitems, &b->ymax, &b->q, &b->spill};
+    const int brc = hip_fail(hipLaunchKernel(batch_bp_kernel_for(b->nt, b->rows, b->rays), dim3(b->grid_b), dim3(b->nt),
+                                             args, b->lds_bytes, s),
+                             "batched back-projection kernel launch");
+    if (brc) return brc;
     bool owners = false;
     for (const auto &sd : b->sys_h) owners = owners || sd.bd.splits > 1;
     if (owners) {
@@ -377,6 +373,8 @@ int tomo_batch_create(const tomo_geometry *systems, int32_t nsystems, tomo_batch
     if (e == hipSuccess) e = hipMemset(b->spill, 0, sizeof(unsigned));
     if (e == hipSuccess && part_floats > 0) e = hipMalloc((void **)&b->part, sizeof(float) * (size_t)part_floats);
     b->rows = 2 * nrows > (int)b->sys_h.size();
+    const int64_t ntab = (int64_t)(table_at.size() - std::count(table_at.begin(), table_at.end(), SIZE_MAX));
+    b->rays = ntab == 0 ? Rays::computed : (ntab == (int64_t)table_at.size() ? Rays::table : Rays::either);
     if (e == hipSuccess && b->rows && kept_pix > 0)
         e = hipMalloc((void **)&b->kept, 2 * sizeof(uint16_t) * (size_t)kept_pix);
     if (e == hipSuccess && brick_floats > 0) e = hipMalloc((void **)&b->bricks, sizeof(float) * (size_t)brick_floats);
@@ -436,7 +434,7 @@ int tomo_batch_create(const tomo_geometry *systems, int32_t nsystems, tomo_batch
             delete b;
             return lrc;
         }
-        const void *kern = batch_bp_kernel_for(b->nt, b->rows);
+        const void *kern = batch_bp_kernel_for(b->nt, b->rows, b->rays);
         if (b->lds_bytes > 65536 &&
             hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->lds_bytes) != hipSuccess) {
             delete b;

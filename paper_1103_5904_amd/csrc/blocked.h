@@ -224,9 +224,9 @@ __device__ inline bool row_interval(const V &v, int row, const float (&lo)[3], c
 // inside it, and the block written once.  bins: nbins 64-bit LDS words plus
 // a dummy.  Called by all NT threads of the workgroup.  kept.cols != null
 // (with kDataMask) takes the passes over kept pixels only, in row-interval
-// footprints.  tab.d != null: each ray's set-up is read from the geometry's
-// ray table instead of computed.
-template <int NT, bool kMapMask, bool kDataMask, bool kObstacle, bool kRows>
+// footprints.  kRays: whether each ray's set-up is computed or read from the
+// geometry's ray table (tab), or either as tab.d says.
+template <int NT, bool kMapMask, bool kDataMask, bool kObstacle, bool kRows, Rays kRays>
 __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict__ views,
                                     const int32_t *__restrict__ frame_views,
                                     const int32_t *__restrict__ frame_voff, const BlockDev &bd,
@@ -432,8 +432,11 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
         // the chunk waits for the wavefront with the most: 128^3 under 28 x
         // 512^2, no table, 1.132 -> 1.094 ms; under 28 x 256^2, from a table,
         // 0.288 -> 0.272 ms).  It loads the next run's pixel values before it
-        // walks, so that the walk hides their latency.  A lane's pixel index
-        // only grows, so its view j and row rr are found by scanning forward.
+        // walks, and the rays' table rows with them, so that the walk hides
+        // their latency (256^3 x 8 batch under 60 x 512^2 with data masks,
+        // table rows and kept columns loaded where they are used: 5.17 -> 4.96
+        // ms).  A lane's pixel index only grows, so its view j and row rr are
+        // found by scanning forward.
         int j = 0, rr = 0;
         // returns true when the pixel comes from a row's run of kept pixels
         // (its data mask need not be read)
@@ -479,45 +482,63 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
             if ((tid & 63) == 0) t = __hip_atomic_fetch_add(&sh.next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             return 64 * (int64_t)__builtin_amdgcn_readfirstlane(t);
         };
-        int64_t run = next_run(), L = run + (tid & 63);
-        int col = 0, row = 0;
-        bool ok = L < total;
-        int jn = 0;
-        int64_t pixn = 0;
+        // A lane's pixel of a run, found two runs ahead (a kept pixel's column
+        // is a load of its own), and what its ray needs from memory, loaded one
+        // run ahead.
+        struct Spot {
+            bool ok, known;
+            int j, row, col;
+        };
+        const auto find = [&](int64_t run) {
+            Spot s;
+            const int64_t L = run + (tid & 63);
+            s.ok = L < total;
+            s.known = false;
+            s.j = s.row = s.col = 0;
+            if (s.ok) {
+                s.known = locate(L, s.col, s.row);
+                s.j = j;
+            }
+            return s;
+        };
+        constexpr bool kTable = kRays == Rays::table;
         float ynext = 0.0f;
         bool mnext = true;
-        if (ok) {
-            const bool known = locate(L, col, row);
-            jn = j;
-            pixn = sh.view[j].pix_off + (int64_t)row * sh.view[j].ncol + col;
-            ynext = images[pixn];
-            if (kDataMask && !known) mnext = data_mask[pixn] != 0;
-        }
+        RayRow next = {};
+        const auto load = [&](const Spot &s) {
+            if (!s.ok) return;
+            const int64_t pix = sh.view[s.j].pix_off + (int64_t)s.row * sh.view[s.j].ncol + s.col;
+            ynext = images[pix];
+            mnext = kDataMask && !s.known ? data_mask[pix] != 0 : true;
+            if constexpr (kTable) next = ray_table_load(tab, pix);
+        };
+        int64_t run = next_run();
+        Spot at = find(run);
+        load(at);
+        int64_t run2 = next_run();
+        Spot at2 = find(run2);
         while (run < total) {
-            const int pcol = col, prow = row, pj = jn;
-            const int64_t ppix = pixn;
-            const bool pok = ok, pm = mnext;
+            const Spot s = at;
             const float yv = ynext;
-            run = next_run();
-            L = run + (tid & 63);
-            ok = L < total;
-            if (ok) {
-                const bool known = locate(L, col, row);
-                jn = j;
-                pixn = sh.view[j].pix_off + (int64_t)row * sh.view[j].ncol + col;
-                ynext = images[pixn];
-                mnext = true;
-                if (kDataMask && !known) mnext = data_mask[pixn] != 0;
-            }
-            if (!pok || !nonzero_bits(yv) || (kDataMask && !pm)) continue;
-            const StagedView &v = sh.view[pj];
+            const bool live = s.ok && nonzero_bits(yv) && (!kDataMask || mnext);
             RayState r;
             RayAxes ax;
-            if (tab.d) {
-                if (!ray_table_get(tab, ppix, r, ax)) continue;
-            } else if (!ray_setup<kObstacle>(g, v, pcol, prow, r, &ax)) {
-                continue;
+            bool meets = true;
+            if constexpr (kTable) meets = ray_table_take(next, r, ax);
+            load(at2);
+            at = at2;
+            run = run2;
+            run2 = next_run();
+            at2 = find(run2);
+            if (!live) continue;
+            const StagedView &v = sh.view[s.j];
+            if constexpr (!kTable) {
+                if (kRays == Rays::either && tab.d)
+                    meets = ray_table_take(ray_table_load(tab, v.pix_off + (int64_t)s.row * v.ncol + s.col), r, ax);
+                else
+                    meets = ray_setup<kObstacle>(g, v, s.col, s.row, r, &ax);
             }
+            if (!meets) continue;
             // parameter interval [E, X) inside the block, exact on the ray's grid
             double E = 0.0, X = r.send;
             bool hit = true;

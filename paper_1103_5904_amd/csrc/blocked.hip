@@ -135,7 +135,7 @@ int ray_table_build(const Plan &p, void *mem, RayTable &out, hipStream_t s)
     return hip_fail(hipGetLastError(), "ray table kernel launch");
 }
 
-template <int NT, bool kMapMask, bool kDataMask, bool kObstacle, bool kRows>
+template <int NT, bool kMapMask, bool kDataMask, bool kObstacle, bool kRows, Rays kRays>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_backproject_blocked(
     GridDev g, const ViewDev *__restrict__ views, const int32_t *__restrict__ frame_views,
     const int32_t *__restrict__ frame_voff, BlockDev bd, Bundle bun, const float *__restrict__ images,
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const int64_t nitems = (int64_t)bd.nb[0] * bd.nb[1] * bd.nb[2] * g.nframes * bd.splits;
     const int64_t item = xcd_order(bun.xcd_remap, blockIdx.x, gridDim.x);
     if (item >= nitems) return;
-    blocked_item<NT, kMapMask, kDataMask, kObstacle, kRows>(g, views, frame_views, frame_voff, bd, item, images,
+    blocked_item<NT, kMapMask, kDataMask, kObstacle, kRows, kRays>(g, views, frame_views, frame_voff, bd, item, images,
                                                             map_mask, data_mask, kept, ymax_parts, out, accumulate,
                                                             spill, tab, bins, sh);
 }
@@ -297,13 +297,18 @@ static int launch_blocked_nt(const Plan &p, const tomo_geometry *g, const BlockD
                              const int *done_flag, const RayTable &tab)
 {
     int rc = TOMO_OK;
-#define TOMO_LAUNCH_BK4(M, D, O, R)                                                                             \
-    do {                                                                                                        \
-        rc = allow_lds(k_backproject_blocked<NT, M, D, O, R>, lds);                                             \
-        if (!rc)                                                                                                \
-            hipLaunchKernelGGL((k_backproject_blocked<NT, M, D, O, R>), dim3((unsigned)bs.items), dim3(NT), lds, \
-                               s, p.grid, p.views_d, p.frame_views_d, p.frame_voff_d, bd, bun, images,          \
-                               g->map_mask, g->data_mask, kept, ymax, dst, acc, done_flag, p.spill_d, tab);    \
+#define TOMO_LAUNCH_BK5(M, D, O, R, T)                                                                             \
+    do {                                                                                                           \
+        rc = allow_lds(k_backproject_blocked<NT, M, D, O, R, T>, lds);                                             \
+        if (!rc)                                                                                                   \
+            hipLaunchKernelGGL((k_backproject_blocked<NT, M, D, O, R, T>), dim3((unsigned)bs.items), dim3(NT), lds, \
+                               s, p.grid, p.views_d, p.frame_views_d, p.frame_voff_d, bd, bun, images,             \
+                               g->map_mask, g->data_mask, kept, ymax, dst, acc, done_flag, p.spill_d, tab);       \
+    } while (0)
+#define TOMO_LAUNCH_BK4(M, D, O, R)                      \
+    do {                                                 \
+        if (tab.d) TOMO_LAUNCH_BK5(M, D, O, R, Rays::table); \
+        else TOMO_LAUNCH_BK5(M, D, O, R, Rays::computed);   \
     } while (0)
 #define TOMO_LAUNCH_BK3(M, D, O)                       \
     do {                                               \
@@ -322,6 +327,7 @@ static int launch_blocked_nt(const Plan &p, const tomo_geometry *g, const BlockD
 #undef TOMO_LAUNCH_BK
 #undef TOMO_LAUNCH_BK3
 #undef TOMO_LAUNCH_BK4
+#undef TOMO_LAUNCH_BK5
     return rc ? rc : hip_fail(hipGetLastError(), "blocked back-projection kernel launch");
 }
 

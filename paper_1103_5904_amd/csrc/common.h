@@ -201,6 +201,10 @@ tomo_tuning untuned_for(const Plan &p);
 // there is one, else untuned_for.
 tomo_tuning tuning_for(const Plan &p);
 
+// Where the blocked P^T takes a ray's set-up from: computed for each block it meets, read from
+// the geometry's ray table, or (a batch of both) decided per item.
+enum class Rays { computed, table, either };
+
 // Per-ray results of the ray set-up over a whole geometry, for launches
 // that would otherwise redo the set-up of one ray many times (the blocked
 // P^T sets a ray up once per block it crosses).  Built once for a geometry

@@ -230,25 +230,34 @@ __device__ inline void ray_table_put(double *__restrict__ d, uint64_t *__restric
     k[i] = w;
 }
 
-// The set-up of pixel i read back from a ray table: the fields of r and ax
-// that the blocked P^T uses (r.s, r.ds, r.send, r.dn, the signs of r.st;
-// ax.idx, ax.rds), bit for bit as ray_setup left them.  False: the ray
-// misses the box.
-__device__ inline bool ray_table_get(const RayTable &t, int64_t i, RayState &r, RayAxes &ax)
+// Row i of a ray table as loaded, and what a walk from it starts with (r's s,
+// ds, st = +-1 or 0, send, dn and ax.idx, ax.rds), bit for bit as ray_setup
+// left them.  False: the ray misses the box.  Apart, so that a row can be
+// loaded well before it is used.
+struct RayRow {
+    double d[kRayTableCols];
+    uint64_t k;
+};
+__device__ inline RayRow ray_table_load(const RayTable &t, int64_t i)
 {
-    const double *__restrict__ d = t.d;
-    const int64_t n = t.n;
-    const uint64_t w = t.k[i];
+    RayRow w;
+#pragma unroll
+    for (int c = 0; c < kRayTableCols; ++c) w.d[c] = t.d[c * t.n + i];
+    w.k = t.k[i];
+    return w;
+}
+__device__ inline bool ray_table_take(const RayRow &w, RayState &r, RayAxes &ax)
+{
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        r.s[a] = d[a * n + i];
-        r.ds[a] = d[(3 + a) * n + i];
-        ax.rds[a] = d[(8 + a) * n + i];
-        ax.idx[a] = (int)((w >> (kRayTableSideBits * a)) & ((1u << kRayTableSideBits) - 1u));
-        r.st[a] = r.ds[a] == 0.0 ? 0 : (((w >> (60 + a)) & 1u) ? 1 : -1);
+        r.s[a] = w.d[a];
+        r.ds[a] = w.d[3 + a];
+        ax.rds[a] = w.d[8 + a];
+        ax.idx[a] = (int)((w.k >> (kRayTableSideBits * a)) & ((1u << kRayTableSideBits) - 1u));
+        r.st[a] = r.ds[a] == 0.0 ? 0 : (((w.k >> (60 + a)) & 1u) ? 1 : -1);
     }
-    r.send = d[6 * n + i];
-    r.dn = d[7 * n + i];
+    r.send = w.d[6];
+    r.dn = w.d[7];
     return r.send > 0.0;
 }
 
