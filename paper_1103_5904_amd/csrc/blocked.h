@@ -144,6 +144,8 @@ struct BlockedShared {
     StagedView view[C];
     int rect[C][4];                      // c0, c1, r0, r1 (c0 > c1: the block is not seen)
     int rows[C];                         // 1: walk the row intervals, 0: the whole rectangle
+    uint32_t ymax[NT / 64];              // the wavefronts' shares of the scale's ingredients
+    int64_t rays[NT / 64];
     int next;                            // runs of 64 pixels handed out
     int64_t vpre[C + 1];                 // pixels of the chunk's views before view j
     uint16_t cs[kRows ? C : 1][kRowsMax];      // first column (or kept-pixel index) of each row's run
@@ -241,6 +243,13 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
     constexpr int C = Sh::C;
     static_assert(8 * C <= NT, "eight lanes per staged view");
     const int tid = threadIdx.x;
+    // What comes before the first run and after the last is a chain of waits
+    // with few wavefronts to fill them, so the scale's maxima, the rows' and
+    // the views' running counts are each one load or scan across lanes (as
+    // loops of one lane or of every lane alike, and a division apiece for the
+    // voxels written at the end, an item took 9% longer: 256^3 x 8 batch under
+    // 60 x 512^2 4.96 -> 4.53 ms; 128^3 under 28 x 256^2, from a table, 0.271
+    // -> 0.257 ms).
     // ---- item -> (frame, block, split)
     const int64_t nblk = (int64_t)bd.nb[0] * bd.nb[1] * bd.nb[2];
     const int split = (int)(item % bd.splits);
@@ -257,18 +266,41 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
 
     const int v0 = frame_voff[frame], v1 = frame_voff[frame + 1];
 
-    // ---- fixed-point scale from the views this owner handles (uniform):
-    // the largest |gain y| among them
-    uint32_t ybits = 0u;
-    double rays = 0.0;
-    for (int k = v0 + split; k < v1; k += bd.splits) {
-        const int vi = frame_views[k];
-        for (int p = 0; p < kYmaxParts; ++p) {
-            const uint32_t b = ymax_parts[vi * kYmaxParts + p];
-            ybits = b > ybits ? b : ybits;
+    const int nvi = v1 - v0 > split ? (v1 - v0 - split + bd.splits - 1) / bd.splits : 0;  // owner's views
+
+    // ---- fixed-point scale from the views this owner handles: the largest
+    // |gain y| among them and their rays
+    {
+        uint32_t m = 0u;
+        for (int q = tid; q < nvi * kYmaxParts; q += NT) {
+            const uint32_t b = ymax_parts[frame_views[v0 + split + q / kYmaxParts * bd.splits] * kYmaxParts + q % kYmaxParts];
+            m = b > m ? b : m;
         }
-        rays += (double)views[vi].ncol * (double)views[vi].nrow;
+        int64_t n = 0;
+        for (int q = tid; q < nvi; q += NT) {
+            const ViewDev &v = views[frame_views[v0 + split + q * bd.splits]];
+            n += (int64_t)v.ncol * v.nrow;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint32_t t = (uint32_t)__shfl_xor((int)m, o);
+            m = t > m ? t : m;
+            n += __shfl_xor(n, o);
+        }
+        if ((tid & 63) == 0) {
+            sh.ymax[tid >> 6] = m;
+            sh.rays[tid >> 6] = n;
+        }
     }
+    __syncthreads();  // (the previous item of this workgroup is done with the bins, too)
+    uint32_t ybits = 0u;
+    int64_t nrays = 0;
+    for (int w = 0; w < NT / 64; ++w) {
+        ybits = sh.ymax[w] > ybits ? sh.ymax[w] : ybits;
+        nrays += sh.rays[w];
+    }
+    ybits = (uint32_t)__builtin_amdgcn_readfirstlane((int)ybits);
+    const double rays = (double)nrays;
     const bool finite = ybits < 0x7f800000u;
     const double ymax = (double)__builtin_bit_cast(float, ybits);
     const double vdiag = sqrt(g.delta[0] * g.delta[0] + g.delta[1] * g.delta[1] + g.delta[2] * g.delta[2]);
@@ -279,18 +311,16 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
     int eb = 0, e1 = 0;
     (void)frexp(fmax(rays, 1.0) * vdiag * ymax * 1.0000001, &eb);
     (void)frexp(vdiag * ymax * 1.0000001, &e1);
-    eb = eb > e1 + 11 ? eb : e1 + 11;
+    eb = __builtin_amdgcn_readfirstlane(eb > e1 + 11 ? eb : e1 + 11);
     const double fx_scale = ldexp(1.0, 61 - eb), fx_inv = ldexp(1.0, eb - 61);
     // bins as LDS byte addresses: bin l at bbase + 8 l (the FP32 bins of
     // non-finite data in the low half of the same word); blim is the dummy bin
     const uint32_t bbase = lds_address(bins), blim = bbase + 8u * (uint32_t)nbins;
 
-    __syncthreads();  // the previous item of this workgroup is done with the bins
     for (int i = tid; i <= nbins; i += NT) bins[i] = 0ull;  // + the dummy bin
     unsigned spills = 0u;
     const bool compact = kRows && kDataMask && kept.cols != nullptr;
 
-    const int nvi = v1 - v0 > split ? (v1 - v0 - split + bd.splits - 1) / bd.splits : 0;  // owner's views
     for (int cs0 = 0; cs0 < nvi; cs0 += C) {
         const int nch = min(C, nvi - cs0);
         // ---- footprints: thread 8 j + c projects corner c of the chunk's
@@ -370,58 +400,72 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
         __syncthreads();
 
         if constexpr (kRows) {
-            // ---- row intervals: one row per thread, widths first (in pre[row + 1])
+            // ---- row intervals: one row per lane, a wavefront per view, which
+            // then sums its rows' widths
+            static_assert(kRowsMax == 64, "a lane per row");
             for (int t = tid; t < nch * kRowsMax; t += NT) {
                 const int j = t / kRowsMax, rr = t % kRowsMax;
                 const int c0 = sh.rect[j][0], c1 = sh.rect[j][1], r0 = sh.rect[j][2], r1 = sh.rect[j][3];
-                if (!sh.rows[j] || rr > r1 - r0) continue;
-                const StagedView &v = sh.view[j];
-                // the block's box less the observer, padded by 1e-3 of a voxel
-                // plus 1e-5 of the largest coordinate in play: far above the FP32
-                // rounding of the interval (relative 1e-7 of these magnitudes) and
-                // the rays' FP64 set-up, so that every ray the exact set-up finds
-                // inside the block is kept
-                float lo[3], hi[3];
+                if (!sh.rows[j]) continue;
+                int width = 0;
+                if (rr <= r1 - r0) {
+                    const StagedView &v = sh.view[j];
+                    // the block's box less the observer, padded by 1e-3 of a voxel
+                    // plus 1e-5 of the largest coordinate in play: far above the FP32
+                    // rounding of the interval (relative 1e-7 of these magnitudes) and
+                    // the rays' FP64 set-up, so that every ray the exact set-up finds
+                    // inside the block is kept
+                    float lo[3], hi[3];
+    #pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        const double big = fmax(fmax(fabs(g.lo[a]), fabs(g.hi[a])), fabs(v.o[a]));
+                        const double pad = 1e-3 * g.delta[a] + 1e-5 * big;
+                        lo[a] = (float)((g.lo[a] + (double)blo[a] * g.delta[a] - pad) - v.o[a]);
+                        hi[a] = (float)((g.lo[a] + (double)bhi[a] * g.delta[a] + pad) - v.o[a]);
+                    }
+                    int a0 = c0, a1 = c1;
+                    if (!row_interval(v, r0 + rr, lo, hi, c0, c1, a0, a1)) {
+                        a0 = c0;
+                        a1 = c1;
+                    }
+                    int start = a0;
+                    width = a1 >= a0 ? a1 - a0 + 1 : 0;
+                    if (compact && width > 0) {  // the run of kept pixels in [a0, a1]
+                        const int64_t rb = v.pix_off + (int64_t)(r0 + rr) * v.ncol;
+                        start = kept.pre[rb + a0];
+                        width = (int)kept.pre[rb + a1] + (data_mask[rb + a1] ? 1 : 0) - start;
+                    }
+                    sh.cs[j][rr] = (uint16_t)start;
+                }
 #pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    const double big = fmax(fmax(fabs(g.lo[a]), fabs(g.hi[a])), fabs(v.o[a]));
-                    const double pad = 1e-3 * g.delta[a] + 1e-5 * big;
-                    lo[a] = (float)((g.lo[a] + (double)blo[a] * g.delta[a] - pad) - v.o[a]);
-                    hi[a] = (float)((g.lo[a] + (double)bhi[a] * g.delta[a] + pad) - v.o[a]);
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int up = __shfl_up(width, o);
+                    if (rr >= o) width += up;
                 }
-                int a0 = c0, a1 = c1;
-                if (!row_interval(v, r0 + rr, lo, hi, c0, c1, a0, a1)) {
-                    a0 = c0;
-                    a1 = c1;
-                }
-                int start = a0, width = a1 >= a0 ? a1 - a0 + 1 : 0;
-                if (compact && width > 0) {  // the run of kept pixels in [a0, a1]
-                    const int64_t rb = v.pix_off + (int64_t)(r0 + rr) * v.ncol;
-                    start = kept.pre[rb + a0];
-                    width = (int)kept.pre[rb + a1] + (data_mask[rb + a1] ? 1 : 0) - start;
-                }
-                sh.cs[j][rr] = (uint16_t)start;
                 sh.pre[j][rr + 1] = width;
-            }
-            __syncthreads();
-            if (tid < nch && sh.rows[tid]) {  // running counts
-                const int j = tid, h = sh.rect[j][3] - sh.rect[j][2] + 1;
-                sh.pre[j][0] = 0;
-                for (int rr = 1; rr <= h; ++rr) sh.pre[j][rr] += sh.pre[j][rr - 1];
+                if (rr == 0) sh.pre[j][0] = 0;
             }
             __syncthreads();
         }
-        if (tid == 0) {  // the chunk's views back to back
-            int64_t acc = 0;
-            for (int j = 0; j < nch; ++j) {
-                sh.vpre[j] = acc;
-                const int c0 = sh.rect[j][0], c1 = sh.rect[j][1], r0 = sh.rect[j][2], r1 = sh.rect[j][3];
+        if (tid < 64) {  // the chunk's views back to back
+            static_assert(C <= 64, "a lane per view");
+            int64_t n = 0;
+            if (tid < nch) {
+                const int c0 = sh.rect[tid][0], c1 = sh.rect[tid][1], r0 = sh.rect[tid][2], r1 = sh.rect[tid][3];
                 if (c0 <= c1 && r0 <= r1)
-                    acc += (kRows && sh.rows[j]) ? (int64_t)sh.pre[j][r1 - r0 + 1]
-                                                 : (int64_t)(c1 - c0 + 1) * (r1 - r0 + 1);
+                    n = (kRows && sh.rows[tid]) ? (int64_t)sh.pre[tid][r1 - r0 + 1]
+                                                : (int64_t)(c1 - c0 + 1) * (r1 - r0 + 1);
             }
-            sh.vpre[nch] = acc;
-            sh.next = 0;
+#pragma unroll
+            for (int o = 1; o < C; o <<= 1) {
+                const int64_t up = __shfl_up(n, o);
+                if (tid >= o) n += up;
+            }
+            if (tid < nch) sh.vpre[tid + 1] = n;
+            if (tid == 0) {
+                sh.vpre[0] = 0;
+                sh.next = 0;
+            }
         }
         __syncthreads();
         const int64_t total = sh.vpre[nch];
@@ -622,8 +666,11 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
     const int nin = ex * ey * ez;
     const int64_t fbase = (int64_t)frame * g.nvox;
     const int64_t total = g.nvox * g.nframes;
+    // thread tid's voxels are NT apart: their coordinates advance by NT's
+    // digits in the block's extents
+    const int sx = NT % ex, sy = (NT / ex) % ey, sz = NT / (ex * ey);
+    int lx = tid % ex, ly = (tid / ex) % ey, lz = tid / (ex * ey);
     for (int e = tid; e < nin; e += NT) {
-        const int lx = e % ex, ly = (e / ex) % ey, lz = e / (ex * ey);
         const int l = (lz * bd.b[1] + ly) * bd.b[0] + lx;
         const float val = finite ? (float)((double)(long long)bins[l] * fx_inv)
                                  : *reinterpret_cast<const float *>(bins + l);
@@ -634,6 +681,17 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
             out[fbase + off] = o;
         } else {
             out[(int64_t)split * total + fbase + off] = val;
+        }
+        lx += sx;
+        ly += sy;
+        lz += sz;
+        if (lx >= ex) {
+            lx -= ex;
+            ++ly;
+        }
+        if (ly >= ey) {
+            ly -= ey;
+            ++lz;
         }
     }
 }
