@@ -276,6 +276,16 @@ static int build_plan(const tomo_geometry *g, int64_t npix, Plan &p)
         std::nth_element(ratio.begin(), ratio.begin() + ratio.size() / 2, ratio.end());
         const double med = ratio[ratio.size() / 2];
         p.bp_rows = med >= 1.4;
+        // Lanes next to each other in a wavefront of the blocked P^T take
+        // pixels 2^bp_pitch apart: lines of sight through the same voxel queue
+        // up for its bin (64 adds to distinct bins take 7.5 cycles of a CU,
+        // with two lanes to a bin 13, four 29, eight 61), but the steps of
+        // lanes further apart differ more.  The lines lie where the times
+        // cross, at that ratio of voxel to pixel (pitch 1 / 2 / 4 / 8, us):
+        // 128^3 under 16 views: 2.1: 252 / 256 / 273, 2.4: 315 / 306 / 318,
+        // 3.5: 667 / 570 / 584, 5: 1438 / 1184 / 1107 / 1130; 64^3: 3.0: 115 /
+        // 97 / 94, 3.5: 145 / 124 / 112 / 115, 6.5: 462 / 422 / 337 / 299.
+        p.bp_pitch = med < 2.3 ? 0 : (med < 3.3 ? 1 : (med < 6.0 ? 2 : 3));
         const double side = std::min(gd.delta[0], std::min(gd.delta[1], gd.delta[2]));
         p_defaults(g, npix, gd, med * side / vox, p.p_auto);
     }

@@ -331,6 +331,7 @@ int tomo_batch_create(const tomo_geometry *systems, int32_t nsystems, tomo_batch
             sd.bd.nb[a] = bs.nb[a];
         }
         sd.bd.splits = bs.splits;
+        sd.bd.pitch = p->bp_pitch;
         sd.bd.maxit = bs.b[0] + bs.b[1] + bs.b[2] + 3;
         sd.nviews = p->nviews;
         sd.p_log2_bw = tu.p_bundle;

@@ -471,7 +471,7 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
         const int64_t total = sh.vpre[nch];
 
         // ---- the footprint pixels of all the chunk's views: a wavefront takes
-        // the next run of 64 neighbouring pixels from a counter as it finishes
+        // the next run of 64 pixels from a counter as it finishes
         // one, since runs differ in the steps they take (shared out in advance,
         // the chunk waits for the wavefront with the most: 128^3 under 28 x
         // 512^2, no table, 1.132 -> 1.094 ms; under 28 x 256^2, from a table,
@@ -524,7 +524,11 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
         const auto next_run = [&]() {
             int t = 0;
             if ((tid & 63) == 0) t = __hip_atomic_fetch_add(&sh.next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            return 64 * (int64_t)__builtin_amdgcn_readfirstlane(t);
+            return __builtin_amdgcn_readfirstlane(t);
+        };
+        // a run's first pixel: 2^pitch runs interleave over as many times 64 pixels
+        const auto first = [&](int run) {
+            return (int64_t)(run >> bd.pitch << bd.pitch) * 64 + (run & ((1 << bd.pitch) - 1));
         };
         // A lane's pixel of a run, found two runs ahead (a kept pixel's column
         // is a load of its own), and what its ray needs from memory, loaded one
@@ -533,9 +537,9 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
             bool ok, known;
             int j, row, col;
         };
-        const auto find = [&](int64_t run) {
+        const auto find = [&](int run) {
             Spot s;
-            const int64_t L = run + (tid & 63);
+            const int64_t L = first(run) + ((tid & 63) << bd.pitch);
             s.ok = L < total;
             s.known = false;
             s.j = s.row = s.col = 0;
@@ -556,12 +560,12 @@ __device__ inline void blocked_item(const GridDev &g, const ViewDev *__restrict_
             mnext = kDataMask && !s.known ? data_mask[pix] != 0 : true;
             if constexpr (kTable) next = ray_table_load(tab, pix);
         };
-        int64_t run = next_run();
+        int run = next_run();
         Spot at = find(run);
         load(at);
-        int64_t run2 = next_run();
+        int run2 = next_run();
         Spot at2 = find(run2);
-        while (run < total) {
+        while (first(run) < total) {
             const Spot s = at;
             const float yv = ynext;
             const bool live = s.ok && nonzero_bits(yv) && (!kDataMask || mnext);

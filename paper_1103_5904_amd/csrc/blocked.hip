@@ -366,6 +366,7 @@ int launch_backproject_blocked(const Plan &p, const tomo_geometry *g, const floa
         bd.nb[a] = bs.nb[a];
     }
     bd.splits = bs.splits;
+    bd.pitch = p.bp_pitch;
     bd.maxit = bs.b[0] + bs.b[1] + bs.b[2] + 3;
     const Bundle bun{tu.bp_bundle, tu.bp_xcd_remap};
     float *dst = bs.splits == 1 ? cube : sc.part;

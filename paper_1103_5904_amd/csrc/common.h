@@ -59,6 +59,7 @@ struct BlockDev {
     int32_t nb[3];    // blocks per axis
     int32_t splits;   // owners per block (views dealt round-robin)
     int32_t maxit;    // bound on in-block segments per ray
+    int32_t pitch;    // log2 of the pixels between a wavefront's neighbouring lanes
 };
 
 // Raw buffer resource over [base, base + bytes): loads outside the range
@@ -163,6 +164,7 @@ struct Plan {
     int32_t *frame_views_d = nullptr;  // device [nviews]: view indices grouped by frame
     int32_t *frame_voff_d = nullptr;   // device [nframes + 1]: offsets into frame_views_d
     int32_t min_frame_views = 0;       // fewest views any frame has
+    int32_t bp_pitch = 0;              // blocked P^T: log2 of the pixels between neighbouring lanes
     bool bp_rows = false;              // blocked P^T walks footprint row intervals (pixels finer than voxels)
     uint64_t size_class = 0;           // key of the autotuner's cache (size_class_of)
     int32_t p_auto[3] = {2, 1, 0};     // P's bundle, tile order and cube layout where the tuning leaves them open
