@@ -288,6 +288,14 @@ static int build_plan(const tomo_geometry *g, int64_t npix, Plan &p)
         p.bp_pitch = med < 2.3 ? 0 : (med < 3.3 ? 1 : (med < 6.0 ? 2 : 3));
         const double side = std::min(gd.delta[0], std::min(gd.delta[1], gd.delta[2]));
         p_defaults(g, npix, gd, med * side / vox, p.p_auto);
+        // Lines of sight further apart than voxels in a cube beyond an XCD's L2:
+        // the x-fastest walk is bound by the lines its gathers bring in, and with
+        // four of a lane's gathers in flight fewer of them are still there for
+        // the lane's next voxel in x (200x100x120 under 16 x 90x80: 74 us with
+        // two, 88 with four; 180x157x103 under 11 x 100x83: 99 and 104;
+        // 105x161x146 under 8 x 131x107: 75 and 76; 260^3 under 27 x 90x65: 305
+        // and 297).
+        p.p_sparse = gd.nvox >= ((int64_t)1 << 20) && med * side / vox < 0.7;
     }
     hipError_t e = hipMalloc((void **)&p.views_d, sizeof(ViewDev) * hv.size());
     if (e != hipSuccess) return set_error(TOMO_ENOMEM, "view table allocation: %s", hipGetErrorString(e));

@@ -51,6 +51,7 @@ struct GridDev {
 struct Bundle {
     int32_t log2_bw;    // 3 -> 8x8, 4 -> 16x4, 2 -> 4x16, 0 -> interleaved
     int32_t xcd_remap;  // tile order (xcd_order): 0 launch order, 1 a run per XCD, 2 runs per XCD in step
+    int32_t sparse = 0; // P's x-fastest walk keeps two gathers in flight instead of four
 };
 
 // Owner-computes P^T launch shape (device copy).
@@ -167,6 +168,7 @@ struct Plan {
     int32_t bp_pitch = 0;              // blocked P^T: log2 of the pixels between neighbouring lanes
     bool bp_rows = false;              // blocked P^T walks footprint row intervals (pixels finer than voxels)
     uint64_t size_class = 0;           // key of the autotuner's cache (size_class_of)
+    bool p_sparse = false;             // P's x-fastest walk keeps two gathers in flight
     int32_t p_auto[3] = {2, 1, 0};     // P's bundle, tile order and cube layout where the tuning leaves them open
     Plan() = default;
     Plan(const Plan &) = delete;

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kThreads) void k_project(
 {
     if (done_flag && *done_flag) return;
     project_tile<kMapMask, kDataMask, kObstacle>(g, views, nviews, bun.log2_bw, block_tile(bun), maxit, cube,
-                                                 map_mask, data_mask, images);
+                                                 map_mask, data_mask, images, bun.sparse != 0);
 }
 
 template <bool kMapMask, bool kDataMask>
@@ -223,7 +223,7 @@ int launch_fill(float *x, int64_t n, float v, hipStream_t s)
 int launch_project_tuned(const Plan &p, const tomo_geometry *g, const float *cube, float *images,
                          bool use_map_mask, hipStream_t s, const int *done_flag, const tomo_tuning &tu)
 {
-    const Bundle b{tu.p_bundle, tu.p_xcd_remap};
+    const Bundle b{tu.p_bundle, tu.p_xcd_remap, p.p_sparse ? 1 : 0};
     const bool mm = use_map_mask && g->map_mask, dm = g->data_mask != nullptr;
     const dim3 grid((unsigned)p.ntiles), blk(kThreads);
 #define TOMO_LAUNCH_P3(M, D, O)                                                                     \
@@ -247,11 +247,18 @@ int launch_project(const Plan &p, const tomo_geometry *g, const float *cube, flo
                    bool use_map_mask, hipStream_t s)
 {
     tomo_tuning tu = tuning_for(p);
-    // a graph under capture holds no allocation of the library's own choosing
+    // The plan's own choice of bricks holds where a solve or a batch keeps the
+    // copy's place.  A single call allocates it, about 18 us of host time: below
+    // 6e7 steps that costs a caller's loop more than bricks win (128x128x80
+    // under 10 x 100^2, 1.7e7 steps: 46 us x-fastest, 55 from bricks; 200x100x120
+    // under 16 x 90x80, 2.4e7: 74 and 76; a gradient of 180x157x103 under 11 x
+    // 100x83, 2.0e7: 353 and 405; 256^3 under 16 x 128^2, 1.0e8: 384 and 335).
+    // And a graph under capture holds no allocation of the library's own choosing.
     if (tu.p_layout >= 2 && current_tuning().p_layout == 0) {
+        const double steps = 0.5 * (double)p.npix * ((double)p.grid.n[0] + p.grid.n[1] + p.grid.n[2]);
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-        if (cap != hipStreamCaptureStatusNone) {
+        if (cap != hipStreamCaptureStatusNone || steps < 6e7) {
             const tomo_tuning open = untuned_for(p);
             if (open.p_layout == tu.p_layout && open.p_bundle == tu.p_bundle && open.p_xcd_remap == tu.p_xcd_remap) {
                 tu.p_bundle = 2;

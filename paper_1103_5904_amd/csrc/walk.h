@@ -567,7 +567,8 @@ template <bool kMapMask, bool kDataMask, bool kObstacle>
 __device__ inline void project_tile(const GridDev &g, const ViewDev *__restrict__ views, int32_t nviews,
                                     int log2_bw, int64_t tile, int32_t maxit,
                                     const float *__restrict__ cube, const uint8_t *__restrict__ map_mask,
-                                    const uint8_t *__restrict__ data_mask, float *__restrict__ images)
+                                    const uint8_t *__restrict__ data_mask, float *__restrict__ images,
+                                    bool sparse = false)
 {
     const LanePixel lp = lane_pixel(views, nviews, tile, log2_bw);
     const ViewDev &v = views[lp.view];
@@ -584,7 +585,8 @@ __device__ inline void project_tile(const GridDev &g, const ViewDev *__restrict_
         const uint32_t last = (uint32_t)(g.nvox - 1);
         const auto rc = make_rsrc(base, wide ? 0u : (uint32_t)(g.nvox * 4));
         double acc;
-        const uint32_t unit = !kMapMask && g.nvox < ((int64_t)1 << 29) ? 4u : 1u;  // offsets in bytes where int32 holds them
+        // offsets in bytes where int32 holds them (and the machine loop walks)
+        const uint32_t unit = !kMapMask && !sparse && g.nvox < ((int64_t)1 << 29) ? 4u : 1u;
         uint32_t pos = (uint32_t)r.off * unit;
         const uint32_t st[3] = {(uint32_t)r.st[0] * unit, (uint32_t)r.st[1] * unit, (uint32_t)r.st[2] * unit};
         const auto plain = [](float x) { return (double)x; };

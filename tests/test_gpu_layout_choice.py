@@ -16,6 +16,7 @@ def _geom(n, nviews, npix, **kw):
 
 
 CASES = [
+    ((128, 104, 80), 24, (150, 141), {}, 2),  # single calls take bricks from 6e7 steps on
     ((128, 104, 80), 4, (140, 131), {}, 2),  # at least 2^20 voxels, rows of 128 bytes
     ((107, 103, 97), 4, (150, 140), {}, 2),  # odd sides, pixels up to 2.5 per voxel
     ((128, 128, 64), 40, (70, 33), {}, 3),  # rays sparser than 0.7 voxels
