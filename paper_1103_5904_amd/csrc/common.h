@@ -263,10 +263,10 @@ int launch_backproject(const Plan &p, const tomo_geometry *g, const float *image
                        bool accumulate, bool use_map_mask, int strategy, hipStream_t s,
                        const int *done_flag = nullptr, void *scratch = nullptr,
                        size_t scratch_bytes = 0, const RayTable *tab = nullptr);
-// P of the plan's tuning without a map mask; a tuning that walks bricks
-// copies the cube into `bricks` (bricked_copy_bytes of them) when given,
-// else into stream-ordered scratch for this launch.
-int launch_project_flagged(const Plan &p, const tomo_geometry *g, const float *cube,
+// P with tuning tu without a map mask; a tuning that walks bricks copies the
+// cube into `bricks` (bricked_copy_bytes for the same tu) when given, else
+// into stream-ordered scratch for this launch.
+int launch_project_flagged(const Plan &p, const tomo_geometry *g, const tomo_tuning &tu, const float *cube,
                            float *images, hipStream_t s, const int *done_flag, float *bricks = nullptr);
 // Bytes of the bricked copy P takes with tuning tu on this plan (0: none).
 size_t bricked_copy_bytes(const Plan &p, const tomo_tuning &tu);
@@ -304,8 +304,6 @@ int launch_backproject_blocked(const Plan &p, const tomo_geometry *g, const floa
                                bool accumulate, bool use_map_mask, hipStream_t s, const int *done_flag,
                                void *scratch, size_t scratch_bytes, const tomo_tuning &tu,
                                const RayTable *tab = nullptr);
-// Strategy a TOMO_BP_* request resolves to under the plan's tuning.
-int resolve_bp_strategy(const Plan &p, int strategy);
 
 // Learned preconditioner network (convnet.hip)
 size_t convnet_forward_ws_bytes(int64_t nvox);

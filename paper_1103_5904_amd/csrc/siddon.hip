@@ -385,10 +385,9 @@ size_t bricked_copy_bytes(const Plan &p, const tomo_tuning &tu)
     return sizeof(float) * (size_t)(bk.frame_stride * p.grid.nframes);
 }
 
-int launch_project_flagged(const Plan &p, const tomo_geometry *g, const float *cube,
+int launch_project_flagged(const Plan &p, const tomo_geometry *g, const tomo_tuning &tu, const float *cube,
                            float *images, hipStream_t s, const int *done_flag, float *bricks)
 {
-    const tomo_tuning tu = tuning_for(p);
     if (tu.p_layout >= 2) {
         BrickDev bk;
         if (bricks && brick_layout(p, tu.p_layout, bk)) {
@@ -399,11 +398,6 @@ int launch_project_flagged(const Plan &p, const tomo_geometry *g, const float *c
         return launch_project_bricked(p, g, cube, images, false, s, done_flag, tu);
     }
     return launch_project_tuned(p, g, cube, images, false, s, done_flag, tu);
-}
-
-int resolve_bp_strategy(const Plan &p, int strategy)
-{
-    return strategy == TOMO_BP_AUTO ? tuning_for(p).bp_default : strategy;
 }
 
 int launch_backproject(const Plan &p, const tomo_geometry *g, const float *images, float *cube,

@@ -786,7 +786,9 @@ struct SolveBuffers {
 // reduction workspace, the blocked P^T's scratch and ray table (when the
 // tuning asks for one), P's bricked copy (when the tuning walks bricks) and
 // the network's activations (flexible CG).  One sequence of allocations
-// serves the solve and the workspace size query.
+// serves the solve and the workspace size query, for the tuning tu: a solve
+// reads its tuning once, and its buffers and every launch go by that one, so
+// that a tuning set or filed by another thread meanwhile changes neither.
 struct CgBufs {
     float *b = nullptr, *r = nullptr, *p = nullptr, *q = nullptr, *img = nullptr, *z = nullptr;
     float *bricks = nullptr;
@@ -799,11 +801,10 @@ struct CgBufs {
 };
 
 static bool cg_buffers(SolveBuffers &buf, const Plan &plan, const tomo_geometry *g, const tomo_cg_params *prm,
-                       CgBufs &o)
+                       const tomo_tuning &tu, CgBufs &o)
 {
     const Dims d = dims_of(g->cube);
     const int64_t n = d.total;
-    const tomo_tuning tu = tuning_for(plan);
     o.b = (float *)buf.alloc(sizeof(float) * n);
     o.r = (float *)buf.alloc(sizeof(float) * n);
     o.p = (float *)buf.alloc(sizeof(float) * n);
@@ -818,7 +819,7 @@ static bool cg_buffers(SolveBuffers &buf, const Plan &plan, const tomo_geometry 
     bool ok = o.b && o.r && o.p && o.q && o.img && o.ws.partials && o.ws.counter && o.ws.cpart && o.ws.st &&
               o.ws.hist;
     // back-projection strategy and its scratch, fixed for the whole solve
-    o.bps = resolve_bp_strategy(plan, prm->bp_strategy);
+    o.bps = prm->bp_strategy == TOMO_BP_AUTO ? tu.bp_default : prm->bp_strategy;
     if (o.bps == TOMO_BP_BLOCKED) {
         o.bscr_bytes = blocked_scratch_bytes(plan, blocked_shape(plan, tu), g->data_mask != nullptr);
         o.bscr = buf.alloc(o.bscr_bytes);
@@ -914,7 +915,7 @@ size_t tomo_cg_workspace_bytes(const tomo_geometry *g, const tomo_cg_params *prm
     SolveBuffers m;
     m.measure = true;
     CgBufs sized;
-    (void)cg_buffers(m, *plan, g, prm, sized);
+    (void)cg_buffers(m, *plan, g, prm, tuning_for(*plan), sized);
     return m.used;
 }
 
@@ -961,13 +962,14 @@ int tomo_cg_solve(const tomo_geometry *g, const float *y_d, float *x_d, const to
     int hrc = height_dev(g->cube, prm->height, hd, "tomo_cg_solve");
     if (hrc) return hrc;
 
+    const tomo_tuning tu = tuning_for(*plan);
     SolveBuffers buf;
     buf.s = s;
     {
         SolveBuffers m;
         m.measure = true;
         CgBufs sized;
-        (void)cg_buffers(m, *plan, g, prm, sized);
+        (void)cg_buffers(m, *plan, g, prm, tu, sized);
         if (prm->workspace) {
             if ((uintptr_t)prm->workspace & 255u)
                 return set_error(TOMO_EINVAL, "tomo_cg_solve: the workspace must be 256-byte aligned");
@@ -987,7 +989,8 @@ int tomo_cg_solve(const tomo_geometry *g, const float *y_d, float *x_d, const to
         }
     }
     CgBufs cb;
-    if (!cg_buffers(buf, *plan, g, prm, cb)) return set_error(TOMO_ENOMEM, "tomo_cg_solve: device allocation failed");
+    if (!cg_buffers(buf, *plan, g, prm, tu, cb))
+        return set_error(TOMO_ENOMEM, "tomo_cg_solve: device allocation failed");
     float *b = cb.b, *r = cb.r, *p = cb.p, *q = cb.q, *img = cb.img, *z = cb.z;
     Workspace ws = cb.ws;
     const int bps = cb.bps;
@@ -1044,15 +1047,15 @@ int tomo_cg_solve(const tomo_geometry *g, const float *y_d, float *x_d, const to
         tab = &tab_v;
     }
     // b = M P^T y
-    rc = launch_backproject(*plan, g, y_d, b, false, true, bps, s, nullptr, bscr, bscr_bytes, tab);
+    rc = launch_backproject_tuned(*plan, g, y_d, b, false, true, bps, s, nullptr, bscr, bscr_bytes, tu, tab);
     if (rc) return rc;
     ++n_bp;
     if (g->map_mask && prm->x0_given) {
         hipLaunchKernelGGL(k_mask, dim3(eb), dim3(kThreads), 0, s, x_d, g->map_mask, d);
     }
     auto apply_A_to = [&](const float *v) -> int {  // q = M (P^T P + prior) v, excluding the prior
-        int e = launch_project_flagged(*plan, g, v, img, s, nullptr, cb.bricks);
-        if (!e) e = launch_backproject(*plan, g, img, q, false, false, bps, s, nullptr, bscr, bscr_bytes, tab);
+        int e = launch_project_flagged(*plan, g, tu, v, img, s, nullptr, cb.bricks);
+        if (!e) e = launch_backproject_tuned(*plan, g, img, q, false, false, bps, s, nullptr, bscr, bscr_bytes, tu, tab);
         n_proj++;
         n_bp++;
         return e;
@@ -1108,11 +1111,11 @@ int tomo_cg_solve(const tomo_geometry *g, const float *y_d, float *x_d, const to
             e2 = evp.get();
             (void)hipEventRecord(e0, s);
         }
-        int e = launch_project_flagged(*plan, g, p, img, s, &ws.st->done, cb.bricks);
+        int e = launch_project_flagged(*plan, g, tu, p, img, s, &ws.st->done, cb.bricks);
         if (timed) (void)hipEventRecord(e1, s);
         if (!e)
-            e = launch_backproject(*plan, g, img, q, bp_acc != 0, false, bps, s, &ws.st->done, bscr, bscr_bytes,
-                                   tab);
+            e = launch_backproject_tuned(*plan, g, img, q, bp_acc != 0, false, bps, s, &ws.st->done, bscr,
+                                         bscr_bytes, tu, tab);
         if (timed) {
             (void)hipEventRecord(e2, s);
             evP.push_back(e0);
