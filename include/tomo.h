@@ -244,14 +244,16 @@ int tomo_trace_ray(const tomo_geometry *g, int32_t view, int32_t col,
  *     k = 2, 3 or 4 = a bricked copy of it, cubes of 2^k voxels a side (the
  *     bricks in x-fastest order, x fastest inside each), made in
  *     stream-ordered scratch at every call.  The copy costs one pass over
- *     the cube; it pays where the cube is far larger than the caches and
- *     the rays are sparser than the voxels, so that a ray's consecutive
- *     gathers would otherwise each fetch a cache line of their own.
- *     While p_bundle, p_xcd_remap and p_layout hold their initial values (2,
- *     1, 0) together, every geometry takes the three that suit its cube and
- *     pixels (tomo_get_class_tuning reports them); the results are the same
- *     bit for bit.  A tomo_project under stream capture then walks the
- *     caller's array.
+ *     the cube; it pays where a wavefront's gathers, or a ray's consecutive
+ *     ones, share more cache lines in bricks than in x-fastest rows, and the
+ *     cube is larger than an XCD's cache.
+ *     -1 (the initial value) = open: with p_bundle 2 and p_xcd_remap 1 beside
+ *     it (their initial values) every geometry takes the three that suit its
+ *     cube and pixels; with others it is 0.  The results are the same bit for
+ *     bit.  tomo_get_class_tuning reports what solves and batches then take; a
+ *     single tomo_project takes the same, but walks the caller's array (2, 1,
+ *     0) under stream capture and where the walk is too short to be worth
+ *     allocating the copy (below 6e7 voxel crossings).
  *   bp_ray_table: 1 = where one geometry serves several blocked
  *     back-projections (tomo_cg_solve, a batch), its rays are set up once
  *     into a table (96 bytes per pixel: in the solve's scratch or workspace,

@@ -29,7 +29,8 @@ static std::mutex g_tuning_mu;
 // 1.27 ms against 1.46 ms for 64x32x2 with 256 lanes on the EUVI-like
 // problem, 5.50 against 6.65 ms on a COR1-like frame).  The binned strategy,
 // which alone takes the bundle field, prefers 8x8 bundles and 4096 bins.
-static tomo_tuning g_tuning = {2, 1, 3, 0, 4096, TOMO_BP_BLOCKED, {128, 32, 2}, 0, 512, 0, 1};
+// P's layout is open (-1): each geometry takes its own (p_defaults).
+static tomo_tuning g_tuning = {2, 1, 3, 0, 4096, TOMO_BP_BLOCKED, {128, 32, 2}, 0, 512, -1, 1};
 
 tomo_tuning current_tuning()
 {
@@ -37,14 +38,24 @@ tomo_tuning current_tuning()
     return g_tuning;
 }
 
-tomo_tuning untuned_for(const Plan &p)
+bool p_open(const tomo_tuning &t) { return t.p_layout < 0 && t.p_bundle == 2 && t.p_xcd_remap == 1; }
+
+tomo_tuning settle_p(const Plan &p, tomo_tuning t, bool single)
 {
-    tomo_tuning t = current_tuning();
-    if (t.p_bundle == 2 && t.p_xcd_remap == 1 && t.p_layout == 0) {
-        t.p_bundle = p.p_auto[0];
-        t.p_xcd_remap = p.p_auto[1];
-        t.p_layout = p.p_auto[2];
-    }
+    const bool open = p_open(t);
+    if (t.p_layout < 0) t.p_layout = 0;
+    if (!open) return t;
+    // The plan's own choice of bricks holds where a solve or a batch keeps the
+    // copy's place.  A single call allocates it, about 18 us of host time: below
+    // 6e7 steps that costs a caller's loop more than bricks win (128x128x80
+    // under 10 x 100^2, 1.7e7 steps: 46 us x-fastest, 55 from bricks; 200x100x120
+    // under 16 x 90x80, 2.4e7: 74 and 76; a gradient of 180x157x103 under 11 x
+    // 100x83, 2.0e7: 353 and 405; 256^3 under 16 x 128^2, 1.0e8: 384 and 335).
+    const double steps = 0.5 * (double)p.npix * ((double)p.grid.n[0] + p.grid.n[1] + p.grid.n[2]);
+    if (single && p.p_auto[2] >= 2 && steps < 6e7) return t;
+    t.p_bundle = p.p_auto[0];
+    t.p_xcd_remap = p.p_auto[1];
+    t.p_layout = p.p_auto[2];
     return t;
 }
 
@@ -430,8 +441,8 @@ int tomo_set_tuning(const tomo_tuning *in)
         return set_error(TOMO_EINVAL, "tomo_set_tuning: bp_splits must be in [0, 64]");
     if (in->bp_threads != 256 && in->bp_threads != 512 && in->bp_threads != 1024)
         return set_error(TOMO_EINVAL, "tomo_set_tuning: bp_threads must be 256, 512 or 1024");
-    if (in->p_layout != 0 && (in->p_layout < 2 || in->p_layout > 4))
-        return set_error(TOMO_EINVAL, "tomo_set_tuning: p_layout must be 0, 2, 3 or 4");
+    if (in->p_layout != -1 && in->p_layout != 0 && (in->p_layout < 2 || in->p_layout > 4))
+        return set_error(TOMO_EINVAL, "tomo_set_tuning: p_layout must be -1, 0, 2, 3 or 4");
     if (in->bp_ray_table != 0 && in->bp_ray_table != 1)
         return set_error(TOMO_EINVAL, "tomo_set_tuning: bp_ray_table must be 0 or 1");
     std::lock_guard<std::mutex> lock(g_tuning_mu);

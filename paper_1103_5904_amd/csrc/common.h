@@ -198,11 +198,16 @@ hipError_t scratch_free(void *p, hipStream_t s);
 int validate_cube(const tomo_cube *c);
 tomo_tuning current_tuning();
 uint64_t size_class_of(const tomo_geometry *g, int64_t npix);
-// The process-wide tuning as it applies to this plan: with P's initial values
-// (2, 1, 0) untouched, P's shape and layout are the plan's own (p_auto).
-tomo_tuning untuned_for(const Plan &p);
-// The tuning launches on this plan use: its size class's autotuned entry if
-// there is one, else untuned_for.
+// Whether a tuning leaves P's shape and layout to the geometry (p_layout -1
+// beside the initial bundle and tile order), and the tuning with them settled:
+// the plan's own choice (p_auto) where it is open, x-fastest where only the
+// layout is.  single: for a call that would allocate the bricked copy itself.
+bool p_open(const tomo_tuning &t);
+tomo_tuning settle_p(const Plan &p, tomo_tuning t, bool single);
+// The plan's size class's autotuned entry if there is one, else the
+// process-wide tuning; P may be open in it.
+tomo_tuning filed_tuning(const Plan &p);
+// filed_tuning with P settled as solves and batches take it.
 tomo_tuning tuning_for(const Plan &p);
 
 // Where the blocked P^T takes a ray's set-up from: computed for each block it meets, read from

@@ -246,25 +246,15 @@ int launch_project_tuned(const Plan &p, const tomo_geometry *g, const float *cub
 int launch_project(const Plan &p, const tomo_geometry *g, const float *cube, float *images,
                    bool use_map_mask, hipStream_t s)
 {
-    tomo_tuning tu = tuning_for(p);
-    // The plan's own choice of bricks holds where a solve or a batch keeps the
-    // copy's place.  A single call allocates it, about 18 us of host time: below
-    // 6e7 steps that costs a caller's loop more than bricks win (128x128x80
-    // under 10 x 100^2, 1.7e7 steps: 46 us x-fastest, 55 from bricks; 200x100x120
-    // under 16 x 90x80, 2.4e7: 74 and 76; a gradient of 180x157x103 under 11 x
-    // 100x83, 2.0e7: 353 and 405; 256^3 under 16 x 128^2, 1.0e8: 384 and 335).
-    // And a graph under capture holds no allocation of the library's own choosing.
-    if (tu.p_layout >= 2 && current_tuning().p_layout == 0) {
-        const double steps = 0.5 * (double)p.npix * ((double)p.grid.n[0] + p.grid.n[1] + p.grid.n[2]);
+    const tomo_tuning filed = filed_tuning(p);
+    tomo_tuning tu = settle_p(p, filed, true);
+    // a graph under capture holds no allocation of the library's own choosing
+    if (p_open(filed) && tu.p_layout >= 2) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-        if (cap != hipStreamCaptureStatusNone || steps < 6e7) {
-            const tomo_tuning open = untuned_for(p);
-            if (open.p_layout == tu.p_layout && open.p_bundle == tu.p_bundle && open.p_xcd_remap == tu.p_xcd_remap) {
-                tu.p_bundle = 2;
-                tu.p_xcd_remap = 1;
-                tu.p_layout = 0;
-            }
+        if (cap != hipStreamCaptureStatusNone) {
+            tu = filed;
+            tu.p_layout = 0;
         }
     }
     return launch_project_with(p, g, cube, images, use_map_mask, s, tu);

@@ -87,15 +87,17 @@ uint64_t size_class_of(const tomo_geometry *g, int64_t npix)
            (ceil_log2((uint64_t)g->nviews) << 16) | ((uint64_t)(c.nframes > 1) << 24);
 }
 
-tomo_tuning tuning_for(const Plan &p)
+tomo_tuning filed_tuning(const Plan &p)
 {
     {
         std::lock_guard<std::mutex> lock(g_class_mu);
         auto it = g_class_tuning.find(p.size_class);
         if (it != g_class_tuning.end()) return it->second;
     }
-    return untuned_for(p);
+    return current_tuning();
 }
+
+tomo_tuning tuning_for(const Plan &p) { return settle_p(p, filed_tuning(p), false); }
 
 static int autotune_impl(const tomo_geometry *g, const float *cube_in, const float *img_in, int32_t reps,
                          tomo_tuning *out, hipStream_t s)
@@ -109,7 +111,7 @@ static int autotune_impl(const tomo_geometry *g, const float *cube_in, const flo
     const bool wide = p.grid.nvox >= ((int64_t)1 << 30);  // the atomic strategies refuse such frames
 
     // candidates
-    const tomo_tuning base = untuned_for(p);
+    const tomo_tuning base = settle_p(p, current_tuning(), false);
     std::vector<tomo_tuning> pc, bc;
     for (int lay : {0, 2, 3, 4})
         for (int bun : {0, 2, 3, 4})
@@ -329,7 +331,8 @@ int tomo_get_class_tuning(const tomo_geometry *g, tomo_tuning *out, int32_t *tun
             found = true;
         }
     }
-    if (!found) *out = untuned_for(*plan);
+    if (!found) *out = current_tuning();
+    *out = settle_p(*plan, *out, false);
     if (tuned) *tuned = found ? 1 : 0;
     return TOMO_OK;
 }
