@@ -23,8 +23,11 @@
 //
 // Each candidate is screened over `reps` launches; the fastest P and P^T
 // candidates are then timed against the process-wide tuning in alternation
-// (five rounds, medians), and a candidate is kept only if it beats that
+// (five rounds, medians; where that leaves P open, against what a single call
+// on this geometry takes), and a candidate is kept only if it beats that
 // tuning there by 1%: the tuner never files a pick slower than the default.
+// Where no P candidate does, P stays as the process-wide tuning has it: open,
+// so that every geometry of the class goes by its own rule.
 #include <math.h>
 
 #include <algorithm>
@@ -111,7 +114,8 @@ static int autotune_impl(const tomo_geometry *g, const float *cube_in, const flo
     const bool wide = p.grid.nvox >= ((int64_t)1 << 30);  // the atomic strategies refuse such frames
 
     // candidates
-    const tomo_tuning base = settle_p(p, current_tuning(), false);
+    const tomo_tuning process = current_tuning();
+    const tomo_tuning base = settle_p(p, process, true);
     std::vector<tomo_tuning> pc, bc;
     for (int lay : {0, 2, 3, 4})
         for (int bun : {0, 2, 3, 4})
@@ -274,7 +278,7 @@ static int autotune_impl(const tomo_geometry *g, const float *cube_in, const flo
         else keep_b = true;  // the process-wide strategy cannot run here
     }
     if (rc) return rc;
-    tomo_tuning win = base;
+    tomo_tuning win = process;
     if (keep_p) {
         win.p_bundle = win_p.p_bundle;
         win.p_xcd_remap = win_p.p_xcd_remap;
@@ -294,7 +298,7 @@ static int autotune_impl(const tomo_geometry *g, const float *cube_in, const flo
         std::lock_guard<std::mutex> lock(g_class_mu);
         g_class_tuning[p.size_class] = win;
     }
-    if (out) *out = win;
+    if (out) *out = settle_p(p, win, false);
     return hip_fail(hipStreamSynchronize(s), "tomo_autotune: synchronise");
 }
 

@@ -76,3 +76,34 @@ def test_settled_bricks_are_walked_by_small_calls_too(tomo):
     own = tomo.class_tuning(dg)[0]
     tomo.set_tuning(p_bundle=own["p_bundle"], p_xcd_remap=own["p_xcd_remap"], p_layout=own["p_layout"])
     assert _bricked(lambda: tomo.project(dg, x)) == [True]
+
+
+BRICKS = ((128, 128, 128), 28, (256, 256))
+ARRAY = ((128, 90, 80), 17, (190, 190))  # the same size class; fewer than 2^20 voxels
+SPARSE = ((128, 128, 70), 30, (72, 60))  # bricks by its rule, and too short for a single call
+TINY = ((70, 30, 20), 20, (70, 64))  # the class of SPARSE; every shape takes a launch's time
+
+
+@pytest.mark.parametrize("tuned,other", [(BRICKS, ARRAY), (ARRAY, BRICKS), (TINY, SPARSE)])
+def test_tuner_leaves_p_open_where_it_keeps_nothing(tomo, tuned, other):
+    """Where no candidate beats the geometry's own choice, the other geometries
+    of its size class keep to their own rule; a pick that is kept is what every
+    call of the class runs, short ones too."""
+    a, b = _ring(tomo, *tuned), _ring(tomo, *other)
+    keys = ("p_bundle", "p_xcd_remap", "p_layout")
+    own_a, own_b = [{k: tomo.class_tuning(g)[0][k] for k in keys} for g in (a, b)]
+    assert (own_a["p_layout"] >= 2) != (own_b["p_layout"] >= 2)
+    x = [to_dev(np.random.default_rng(4).normal(size=g.cube_shape)) for g in (a, b)]
+    alone = [_bricked(lambda: tomo.project(g, v)) for g, v in zip((a, b), x)]
+    chosen = {k: v for k, v in tomo.autotune(a, reps=5).items() if k in keys}
+    print("P before and after tuning:", own_a, chosen, flush=True)
+    (now_a, tuned_a), (now_b, tuned_b) = tomo.class_tuning(a), tomo.class_tuning(b)
+    assert tuned_a and tuned_b
+    assert {k: now_a[k] for k in keys} == chosen
+    now = [_bricked(lambda: tomo.project(g, v)) for g, v in zip((a, b), x)]
+    if chosen == own_a:
+        assert {k: now_b[k] for k in keys} == own_b
+        assert now == alone
+    else:
+        assert {k: now_b[k] for k in keys} == chosen
+        assert now == [[chosen["p_layout"] >= 2]] * 2
