@@ -503,12 +503,16 @@ void tomo_cg_default_params(tomo_cg_params *p);
  * set, its ray table, P's bricked copy of the iterate if the geometry's
  * tuning walks bricks, and the network's activations with a
  * preconditioner).  The figure depends on the launch tuning in effect for
- * g's size class: query again after tomo_autotune or tomo_set_tuning.
+ * g's size class: query again after tomo_autotune or tomo_set_tuning.  A
+ * workspace without the bricked copy's place is accepted where p_layout is
+ * open (-1): P then walks the caller's x-fastest layout, with the same result.
+ * Without a workspace the solve does the same where the device's memory is
+ * short.
  * Returns 0 for invalid arguments and for use_graph = 1 (a batch of one
  * takes its own memory; tomo_cg_solve refuses a workspace with it).  With a
  * workspace the solve allocates no device memory (the first call on a new
- * geometry still uploads its view table, as every call does); a workspace
- * smaller than this figure is rejected with TOMO_EINVAL.
+ * geometry still uploads its view table, as every call does); a smaller
+ * workspace is otherwise rejected with TOMO_EINVAL.
  */
 size_t tomo_cg_workspace_bytes(const tomo_geometry *g, const tomo_cg_params *p);
 
@@ -559,8 +563,11 @@ void tomo_autotune_clear(void);
  *   must stay valid while the batch exists, their view arrays need not.
  * The batch owns its device work queues and scratch, and the ray tables of
  * the systems whose tuning sets bp_ray_table (96 bytes per pixel, built
- * when the batch is created, which then synchronises the device): use it
- * from one stream at a time.  tomo_batch_destroy synchronises the device.
+ * when the batch is created, which then synchronises the device), and the
+ * bricked copies of the systems whose P walks bricks; where that is the
+ * geometry's own choice (p_layout -1) and the device's memory is short for
+ * them or for a solve's vectors, those systems walk the x-fastest layout: use
+ * it from one stream at a time.  tomo_batch_destroy synchronises the device.
  */
 typedef struct tomo_batch_s *tomo_batch;
 int tomo_batch_create(const tomo_geometry *systems, int32_t nsystems,

@@ -46,6 +46,9 @@ struct Operands {
 
 int batch_project_ops(tomo_batch b, const Operands &ops, hipStream_t s);
 int batch_backproject_ops(tomo_batch b, const Operands &ops, hipStream_t s);
+// Gives the memory of open_bricks back: those systems walk x-fastest from then
+// on (the same bits).  False: there is none.
+bool batch_drop_open_bricks(tomo_batch b);
 
 }  // namespace tomo
 
@@ -69,7 +72,11 @@ struct tomo_batch_s {
     int32_t nt = 256;   // lanes per workgroup of the persistent P^T (the dominant system's tuning)
     tomo::Rays rays = tomo::Rays::computed;  // where P^T takes the rays' set-up from
     uint16_t *kept = nullptr;  // kept-pixel rows of the systems' data masks
-    float *bricks = nullptr;   // bricked copies of the cubes of the systems that walk bricks in P
+    // bricked copies of the cubes of the systems that walk bricks in P: of those
+    // whose tuning asks for them, and of those whose geometry's rule does (P left
+    // open), which the batch can do without
+    float *bricks = nullptr, *open_bricks = nullptr;
+    std::vector<bool> p_open;  // P left open: bricks are the geometry's own choice
     char *tables = nullptr;    // ray tables of the systems whose tuning asks for one
     ~tomo_batch_s();
 };

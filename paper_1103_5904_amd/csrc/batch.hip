@@ -192,12 +192,37 @@ tomo_batch_s::~tomo_batch_s()
     if (part) (void)hipFree(part);
     if (kept) (void)hipFree(kept);
     if (bricks) (void)hipFree(bricks);
+    if (open_bricks) (void)hipFree(open_bricks);
     if (tables) (void)hipFree(tables);
     if (spill) (void)hipFree(spill);
     (void)hipSetDevice(cur);
 }
 
 namespace tomo {
+
+// Systems whose P was left open, on the x-fastest walk.
+static void walk_open_x_fastest(tomo_batch b)
+{
+    for (int k = 0; k < b->nsys; ++k) {
+        if (!b->p_open[(size_t)k]) continue;
+        tomo_tuning &tu = b->tunings[(size_t)k];
+        tu.p_bundle = 2;
+        tu.p_xcd_remap = 1;
+        tu.p_layout = 0;
+        b->sys_h[(size_t)k].bricked = nullptr;
+    }
+}
+
+bool batch_drop_open_bricks(tomo_batch b)
+{
+    if (!b->open_bricks) return false;
+    (void)hipGetLastError();  // the allocation that failed
+    (void)hipDeviceSynchronize();
+    (void)hipFree(b->open_bricks);
+    b->open_bricks = nullptr;
+    walk_open_x_fastest(b);
+    return true;
+}
 
 int batch_project_ops(tomo_batch b, const Operands &h, hipStream_t s)
 {
@@ -282,7 +307,7 @@ int tomo_batch_create(const tomo_geometry *systems, int32_t nsystems, tomo_batch
     if (!b) return set_error(TOMO_ENOMEM, "tomo_batch_create: host allocation failed");
     (void)hipGetDevice(&b->device);
     b->nsys = nsystems;
-    int64_t part_floats = 0, kept_pix = 0, brick_floats = 0;
+    int64_t part_floats = 0, kept_pix = 0, brick_floats = 0, open_floats = 0;
     size_t table_bytes = 0;
     std::vector<size_t> table_at;  // offset of each system's ray table (SIZE_MAX: none)
     int nrows = 0;  // systems whose plans ask for footprint row intervals
@@ -296,7 +321,9 @@ int tomo_batch_create(const tomo_geometry *systems, int32_t nsystems, tomo_batch
             return st;
         }
         plans.push_back(p);
-        tunings.push_back(tuning_for(*p));
+        const tomo_tuning filed = filed_tuning(*p);
+        b->p_open.push_back(p_open(filed));
+        tunings.push_back(settle_p(*p, filed, false));
     }
     // One workgroup size and LDS size serve every item of the persistent
     // P^T: the dominant system's (most rays).  The others keep their tuned
@@ -337,7 +364,7 @@ int tomo_batch_create(const tomo_geometry *systems, int32_t nsystems, tomo_batch
         sd.p_log2_bw = tu.p_bundle;
         if (tu.p_layout >= 2 && brick_layout(*p, tu.p_layout, sd.bk)) {
             bricked[(size_t)k] = true;
-            brick_floats += sd.bk.frame_stride * p->grid.nframes;
+            (b->p_open[(size_t)k] ? open_floats : brick_floats) += sd.bk.frame_stride * p->grid.nframes;
         }
         const size_t tb = tu.bp_ray_table ? ray_table_bytes(*p) : 0;
         table_at.push_back(tb ? table_bytes : SIZE_MAX);
@@ -384,13 +411,9 @@ int tomo_batch_create(const tomo_geometry *systems, int32_t nsystems, tomo_batch
         delete b;
         return set_error(TOMO_ENOMEM, "tomo_batch_create: device allocation failed (%s)", hipGetErrorString(e));
     }
-    int64_t off = 0, koff = 0, boff = 0;
+    int64_t off = 0, koff = 0;
     for (size_t k = 0; k < b->sys_h.size(); ++k) {
         SysDev &sd = b->sys_h[k];
-        if (bricked[k]) {
-            sd.bricked = b->bricks + boff;
-            boff += sd.bk.frame_stride * sd.grid.nframes;
-        }
         if (sd.bd.splits > 1) {
             sd.part = b->part + off;
             off += (int64_t)sd.bd.splits * sd.ntot;
@@ -420,6 +443,19 @@ int tomo_batch_create(const tomo_geometry *systems, int32_t nsystems, tomo_batch
     if (e != hipSuccess) {
         delete b;
         return set_error(TOMO_ENOMEM, "tomo_batch_create: system table upload failed (%s)", hipGetErrorString(e));
+    }
+    // the copies that only speed P up, after all that the batch needs
+    if (open_floats > 0 && hipMalloc((void **)&b->open_bricks, sizeof(float) * (size_t)open_floats) != hipSuccess) {
+        (void)hipGetLastError();
+        b->open_bricks = nullptr;
+        walk_open_x_fastest(b);
+    }
+    float *brick_at[2] = {b->bricks, b->open_bricks};
+    for (size_t k = 0; k < b->sys_h.size(); ++k) {
+        float *&at = brick_at[b->p_open[k] ? 1 : 0];
+        if (!bricked[k] || !at) continue;
+        b->sys_h[k].bricked = at;
+        at += b->sys_h[k].bk.frame_stride * b->sys_h[k].grid.nframes;
     }
     // persistent grids: as many workgroups as stay resident, at most one per item
     int cus = 0, per_b = 0;

@@ -843,6 +843,16 @@ static bool cg_buffers(SolveBuffers &buf, const Plan &plan, const tomo_geometry 
     return ok;
 }
 
+// Bytes of one block that holds all of a solve's buffers.
+static size_t cg_bytes(const Plan &plan, const tomo_geometry *g, const tomo_cg_params *prm, const tomo_tuning &tu)
+{
+    SolveBuffers m;
+    m.measure = true;
+    CgBufs sized;
+    (void)cg_buffers(m, plan, g, prm, tu, sized);
+    return m.used;
+}
+
 struct EventPool {
     std::vector<hipEvent_t> ev;
     hipEvent_t get()
@@ -912,11 +922,7 @@ size_t tomo_cg_workspace_bytes(const tomo_geometry *g, const tomo_cg_params *prm
     int st = TOMO_OK;
     PlanRef plan = get_plan(g, &st);
     if (!plan) return 0;
-    SolveBuffers m;
-    m.measure = true;
-    CgBufs sized;
-    (void)cg_buffers(m, *plan, g, prm, tuning_for(*plan), sized);
-    return m.used;
+    return cg_bytes(*plan, g, prm, tuning_for(*plan));
 }
 
 int tomo_cg_solve(const tomo_geometry *g, const float *y_d, float *x_d, const tomo_cg_params *prm,
@@ -962,30 +968,47 @@ int tomo_cg_solve(const tomo_geometry *g, const float *y_d, float *x_d, const to
     int hrc = height_dev(g->cube, prm->height, hd, "tomo_cg_solve");
     if (hrc) return hrc;
 
-    const tomo_tuning tu = tuning_for(*plan);
+    const tomo_tuning filed = filed_tuning(*plan);
+    tomo_tuning tu = settle_p(*plan, filed, false);
     SolveBuffers buf;
     buf.s = s;
     {
-        SolveBuffers m;
-        m.measure = true;
-        CgBufs sized;
-        (void)cg_buffers(m, *plan, g, prm, tu, sized);
+        // P's bricked copy, where it is the geometry's own choice, is done
+        // without when the memory is short: x-fastest gives the same bits
+        size_t need = cg_bytes(*plan, g, prm, tu), least = need;
+        tomo_tuning flat = tu;
+        if (p_open(filed) && tu.p_layout >= 2) {
+            flat = filed;
+            flat.p_layout = 0;
+            least = cg_bytes(*plan, g, prm, flat);
+        }
         if (prm->workspace) {
             if ((uintptr_t)prm->workspace & 255u)
                 return set_error(TOMO_EINVAL, "tomo_cg_solve: the workspace must be 256-byte aligned");
-            if (prm->workspace_bytes < m.used)
+            if (prm->workspace_bytes < least)
                 return set_error(TOMO_EINVAL, "tomo_cg_solve: workspace of %zu bytes, %zu needed",
-                                 prm->workspace_bytes, m.used);
+                                 prm->workspace_bytes, need);
+            if (prm->workspace_bytes < need) tu = flat;
             buf.arena = (char *)prm->workspace;
             buf.arena_bytes = prm->workspace_bytes;
         } else {
             // one block from the pool for all of the solve's buffers: the
             // pool then reuses the same block solve after solve (separate
             // pieces of a few hundred MB were measured to cost ~1 ms a solve)
-            if (scratch_alloc(&buf.owned, m.used, s) != hipSuccess)
-                return set_error(TOMO_ENOMEM, "tomo_cg_solve: device allocation of %zu bytes failed", m.used);
+            hipError_t e = scratch_alloc(&buf.owned, need, s);
+            if (e != hipSuccess && least < need) {
+                (void)hipGetLastError();  // the failed allocation's error is not the caller's
+                tu = flat;
+                need = least;
+                buf.owned = nullptr;
+                e = scratch_alloc(&buf.owned, need, s);
+            }
+            if (e != hipSuccess) {
+                buf.owned = nullptr;
+                return set_error(TOMO_ENOMEM, "tomo_cg_solve: device allocation of %zu bytes failed", need);
+            }
             buf.arena = (char *)buf.owned;
-            buf.arena_bytes = m.used;
+            buf.arena_bytes = need;
         }
     }
     CgBufs cb;
@@ -1246,8 +1269,8 @@ int tomo_cg_solve(const tomo_geometry *g, const float *y_d, float *x_d, const to
 
 // ------------------------------------------------------------ batched CG
 
-int tomo_batch_cg_solve(tomo_batch bt, const float *const *y_d, float *const *x_d, const tomo_cg_params *prm,
-                        tomo_cg_report *rep, tomo_stream stream)
+static int batch_cg(tomo_batch bt, const float *const *y_d, float *const *x_d, const tomo_cg_params *prm,
+                    tomo_cg_report *rep, tomo_stream stream)
 {
     if (!bt || !y_d || !x_d || !prm || !rep) return set_error(TOMO_EINVAL, "tomo_batch_cg_solve: NULL argument");
     const int ns = bt->nsys;
@@ -1646,6 +1669,16 @@ int tomo_batch_cg_solve(tomo_batch bt, const float *const *y_d, float *const *x_
         r.time_kernels = rep[0].time_kernels;
     }
     return TOMO_OK;
+}
+
+int tomo_batch_cg_solve(tomo_batch bt, const float *const *y_d, float *const *x_d, const tomo_cg_params *prm,
+                        tomo_cg_report *rep, tomo_stream stream)
+{
+    const int rc = batch_cg(bt, y_d, x_d, prm, rep, stream);
+    // no memory for the solve's vectors (nothing has run yet): the batch's
+    // copies that only speed P up make room
+    if (rc == TOMO_ENOMEM && batch_drop_open_bricks(bt)) return batch_cg(bt, y_d, x_d, prm, rep, stream);
+    return rc;
 }
 
 }  // extern "C"
