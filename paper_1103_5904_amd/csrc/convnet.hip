@@ -1109,11 +1109,57 @@ __global__ __launch_bounds__(kWThreads) void k_wgrad2(const uint16_t *__restrict
     }
 }
 
+// The two factors of a layer's weight gradient, gw[t] = sum_v f(v) h(v + o_t)
+// over the pairs of voxels inside the volume: f is the layer's data gradient
+// (BF16 [voxel][16]; the output gradient for layer 3, FP32), h its input (BF16
+// [voxel][16]; x for layer 1, FP32).  gb = sum_v f(v).
+struct GradFactors {
+    const uint16_t *fb, *hb;  // BF16 factors (null: the FP32 ones)
+    const float *ff, *hf;
+};
+
+// This thread's share of output o of layer kLayer's gradient, pair by pair in
+// FP64: voxels outside the volume have no part, nor (layer 2) have zeros of f.
+template <int kLayer>
+__device__ inline double grad_by_pairs(int o, const GradFactors &p, const Vol &d)
+{
+    const int nw = (kLayer == 2 ? kC : 1) * kC * kTaps;
+    const bool bias = o >= nw;
+    const int q = bias ? 0 : o / kTaps, t = bias ? 13 : o % kTaps;  // 13: the voxel itself
+    const int cf = kLayer == 3 ? 0 : (bias ? o - nw : (kLayer == 2 ? q / kC : q));
+    const int ch = q % kC;
+    const int ox = t % 3 - 1, oy = (t / 3) % 3 - 1, oz = t / 9 - 1;
+    const int rows = d.ny * d.nz;
+    double acc = 0.0;
+    for (int row = threadIdx.x >> 6; row < rows; row += kThreads / 64) {
+        const int jj = row % d.ny + oy, kk = row / d.ny + oz;
+        if (jj < 0 || jj >= d.ny || kk < 0 || kk >= d.nz) continue;
+        const int64_t vr = (int64_t)row * d.nx, hr = ((int64_t)kk * d.ny + jj) * d.nx + ox;
+        for (int i = threadIdx.x & 63; i < d.nx; i += 64) {
+            if (i + ox < 0 || i + ox >= d.nx) continue;
+            const float f = kLayer == 3 ? p.ff[vr + i] : bf2f(p.fb[(vr + i) * kC + cf]);
+            if (bias) {
+                acc += (double)f;
+            } else if (!(kLayer == 2 && f == 0.0f)) {
+                const float h = kLayer == 1 ? p.hf[hr + i] : bf2f(p.hb[(hr + i) * kC + ch]);
+                acc += (double)f * (double)h;
+            }
+        }
+    }
+    return acc;
+}
+
 // grad[off + o] = sum over blocks of part[b][o], in a fixed order: eight
 // threads per output take the blocks b = k, k + 8, ... and are added in turn.
+// The matrix products also multiply what the sum leaves out, by zeros (voxels
+// of a column outside the volume, zeros of layer 2's data gradient), which an
+// infinite or NaN factor turns into NaN.  Such a factor is in a product of
+// every sum it belongs to as well, so a finite sum is right as it stands, and
+// the others are taken again pair by pair.
 constexpr int kRedOut = 32;
+template <int kLayer>
 __global__ __launch_bounds__(kThreads) void k_reduce_parts(const double *__restrict__ part, int nblocks, int width,
-                                                           float *__restrict__ grad, int off)
+                                                           float *__restrict__ grad, int off, GradFactors factors, Vol d)
 {
     static_assert(kThreads == 8 * kRedOut, "eight threads per output");
     __shared__ double red[8][kRedOut];
@@ -1128,6 +1174,15 @@ __global__ __launch_bounds__(kThreads) void k_reduce_parts(const double *__restr
     if (k == 0 && o < width) {
         for (int q = 1; q < 8; ++q) s += red[q][l];
         grad[off + o] = (float)s;
+        red[0][l] = s;
+    }
+    const bool again = k == 0 && o < width && !isfinite(s);
+    if (!__syncthreads_or(again ? 1 : 0)) return;
+    __shared__ double lds[4];
+    for (int q = 0; q < kRedOut && blockIdx.x * kRedOut + q < width; ++q) {
+        if (isfinite(red[0][q])) continue;
+        const double sum = block_sum(grad_by_pairs<kLayer>(blockIdx.x * kRedOut + q, factors, d), lds);
+        if (threadIdx.x == 0) grad[off + blockIdx.x * kRedOut + q] = (float)sum;
     }
 }
 
@@ -1347,26 +1402,26 @@ static int convnet_train_pass(const tomo_cube *cube, const float *params_d, cons
     }
     March m;
     unsigned nb;
-    auto reduce = [&](unsigned blocks, int width, int off) {
-        hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)((width + kRedOut - 1) / kRedOut)), dim3(kThreads), 0, s, w.part,
-                           (int)blocks, width, grad_d, off);
+    auto reduce = [&](auto layer, unsigned blocks, int width, int off, const GradFactors &f) {
+        hipLaunchKernelGGL(k_reduce_parts<decltype(layer)::value>, dim3((unsigned)((width + kRedOut - 1) / kRedOut)),
+                           dim3(kThreads), 0, s, w.part, (int)blocks, width, grad_d, off, f, d);
     };
     // layer 3
     nb = march_grid(reinterpret_cast<const void *>(k_wgrad_field<false>), d, kZX, kZY, m, kFieldBlocks);
     hipLaunchKernelGGL(k_wgrad_field<false>, dim3(nb), dim3(kThreads), 0, s, w.a2, g_d, d, m, w.part);
-    reduce(nb, kFPart3, OW3);
+    reduce(std::integral_constant<int, 3>{}, nb, kFPart3, OW3, GradFactors{nullptr, w.a2, g_d, nullptr});
     nb = march_grid(reinterpret_cast<const void *>(k_conv3_bwd), d, kBX, kBY, m);
     hipLaunchKernelGGL(k_conv3_bwd, dim3(nb), dim3(kThreads), 0, s, params_d, g_d, w.a2, d, m, w.gh);
     // layer 2 (gh = d loss / d h2)
     nb = march_grid(reinterpret_cast<const void *>(k_wgrad2), d, kWX, kWY, m, kWgBlocks, kWThreads);
     hipLaunchKernelGGL(k_wgrad2, dim3(nb), dim3(kWThreads), 0, s, w.gh, w.a1, d, m, w.part);
-    reduce(nb, kWPart, OW2);
+    reduce(std::integral_constant<int, 2>{}, nb, kWPart, OW2, GradFactors{w.gh, w.a1, nullptr, nullptr});
     // d loss / d h1 = [a1 > 0] conv^T(gh); written over a2 (no longer needed)
     launch_conv16<kMasked>(w.gh, w.fragT, nullptr, d, w.a1, w.a2, noskip, s);
     // layer 1
     nb = march_grid(reinterpret_cast<const void *>(k_wgrad_field<true>), d, kZX, kZY, m, kFieldBlocks);
     hipLaunchKernelGGL(k_wgrad_field<true>, dim3(nb), dim3(kThreads), 0, s, w.a2, x_d, d, m, w.part);
-    reduce(nb, kFPart1, OW1);
+    reduce(std::integral_constant<int, 1>{}, nb, kFPart1, OW1, GradFactors{w.a2, nullptr, nullptr, x_d});
     return hip_fail(hipGetLastError(), "convnet backward launch");
 }
 
