@@ -220,9 +220,10 @@ int tomo_trace_ray(const tomo_geometry *g, int32_t view, int32_t col,
  *     order and takes no bundle shape).
  *   p_xcd_remap, bp_xcd_remap: order of the tiles (of the voxel-block items
  *     for the blocked back-projection) over the 8 XCDs: 0 = launch order,
- *     1 = one contiguous run per XCD, 2 = runs of 32 per XCD with all XCDs
- *     advancing through the list together (a multi-frame cube then keeps one
- *     frame in the caches at a time).
+ *     1 = one contiguous run per XCD, 2 = runs of 32 (P from the caller's
+ *     x-fastest array: 64) per XCD with all XCDs advancing through the list
+ *     together (a multi-frame cube then keeps one frame in the caches at a
+ *     time).
  *   bp_lds_bins: 64-bit LDS bins per workgroup of the binned
  *     back-projection (512..8192, i.e. 4..64 KiB; larger boxes mean fewer
  *     flushes but fewer resident workgroups).

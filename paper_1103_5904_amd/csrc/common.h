@@ -101,27 +101,30 @@ __device__ inline int64_t xcd_remap(int64_t b, int64_t nb)
     return x * q + (x < r ? x : r) + i;
 }
 
-// The same with runs of kXcdChunk: each group of 8 kXcdChunk consecutive
-// workgroup ids covers 8 kXcdChunk consecutive tiles, kXcdChunk of them
-// (contiguous) per XCD.  All XCDs then advance through the tile list
-// together, so the data they touch at one time stays a window of it (one
-// frame of a multi-frame cube, not eight), while each XCD's L2 still sees
-// neighbouring tiles.  The ragged last group keeps the identity.  Bijective
-// on [0, nb).
-constexpr int64_t kXcdChunk = 32;
+// The same with runs of kRun: each group of 8 kRun consecutive workgroup ids
+// covers 8 kRun consecutive tiles, kRun of them (contiguous) per XCD.  All XCDs
+// then advance through the tile list together, so the data they touch at one
+// time stays a window of it (one frame of a multi-frame cube, not eight), while
+// each XCD's L2 still sees neighbouring tiles.  The ragged last group keeps the
+// identity.  Bijective on [0, nb).
+template <int64_t kRun>
 __device__ inline int64_t xcd_remap_chunked(int64_t b, int64_t nb)
 {
-    const int64_t g = b / (8 * kXcdChunk);
-    if ((g + 1) * 8 * kXcdChunk > nb) return b;
-    const int64_t w = b - g * 8 * kXcdChunk;
-    return g * 8 * kXcdChunk + (w & 7) * kXcdChunk + (w >> 3);
+    const int64_t g = b / (8 * kRun);
+    if ((g + 1) * 8 * kRun > nb) return b;
+    const int64_t w = b - g * 8 * kRun;
+    return g * 8 * kRun + (w & 7) * kRun + (w >> 3);
 }
 
 // Tile order of a launch: 0 = launch order, 1 = one contiguous run per
-// XCD, 2 = runs of kXcdChunk per XCD advancing together.
+// XCD, 2 = runs of kRun per XCD advancing together.  Walks from bricks and the
+// blocked P^T take runs of 32 (Thomson pB of a 256^3 frame under 60 x 512^2,
+// bricks: 1904 us, 2267 with runs of 64), walks of the x-fastest cube 64
+// (105x161x146 under 8 x 131x107: 65 us, 77 with 32).
+template <int64_t kRun = 32>
 __device__ inline int64_t xcd_order(int32_t mode, int64_t b, int64_t nb)
 {
-    return mode == 1 ? xcd_remap(b, nb) : (mode == 2 ? xcd_remap_chunked(b, nb) : b);
+    return mode == 1 ? xcd_remap(b, nb) : (mode == 2 ? xcd_remap_chunked<kRun>(b, nb) : b);
 }
 
 // Sum of one double per thread over a 256-thread block; the result is valid

@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kThreads) void k_project_bricked(
     float *__restrict__ images, const int *__restrict__ done_flag)
 {
     if (done_flag && *done_flag) return;
-    project_tile_bricked<kDataMask, kObstacle, false, kWide>(g, views, nviews, bun.log2_bw, block_tile(bun), maxit,
+    project_tile_bricked<kDataMask, kObstacle, false, kWide>(g, views, nviews, bun.log2_bw, block_tile<32>(bun), maxit,
                                                              bricked, bk, data_mask, images);
 }
 
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kThreads) void k_project_bricked_lut(
         lut[e] = brick_axis_term(bk, a, i) * (kWide ? 1u : 4u);
     }
     __syncthreads();
-    project_tile_bricked<kDataMask, kObstacle, true, kWide>(g, views, nviews, bun.log2_bw, block_tile(bun), maxit,
+    project_tile_bricked<kDataMask, kObstacle, true, kWide>(g, views, nviews, bun.log2_bw, block_tile<32>(bun), maxit,
                                                             bricked, bk, data_mask, images, lut);
 }
 

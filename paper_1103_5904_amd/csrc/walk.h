@@ -523,6 +523,9 @@ struct LanePixel {
     int col, row;
 };
 
+// kCurve: the lanes of an 8x8 bundle along a Z-order curve (walks from bricks)
+// instead of by rows.
+template <bool kCurve = false>
 __device__ inline LanePixel lane_pixel(const ViewDev *__restrict__ views, int nviews, int64_t tile,
                                        int log2_bw)
 {
@@ -543,7 +546,7 @@ __device__ inline LanePixel lane_pixel(const ViewDev *__restrict__ views, int nv
         lp.row = ty * kTile + (l >> 3) * 2 + (w >> 1);
         return lp;
     }
-    if (log2_bw == 3) {
+    if (kCurve && log2_bw == 3) {
         const int x = (l & 1) | ((l >> 1) & 2) | ((l >> 2) & 4), y = ((l >> 1) & 1) | ((l >> 2) & 2) | ((l >> 3) & 4);
         lp.col = tx * kTile + (w & 1) * 8 + x;
         lp.row = ty * kTile + (w >> 1) * 8 + y;
@@ -556,9 +559,10 @@ __device__ inline LanePixel lane_pixel(const ViewDev *__restrict__ views, int nv
     return lp;
 }
 
+template <int64_t kRun = 64>
 __device__ inline int64_t block_tile(const Bundle &b)
 {
-    return xcd_order(b.xcd_remap, blockIdx.x, gridDim.x);
+    return xcd_order<kRun>(b.xcd_remap, blockIdx.x, gridDim.x);
 }
 
 // P for one 16x16 tile (all threads of the workgroup): each lane's pixel =
@@ -652,7 +656,7 @@ __device__ inline void project_tile_bricked(const GridDev &g, const ViewDev *__r
                                             const BrickDev &bk, const uint8_t *__restrict__ data_mask,
                                             float *__restrict__ images, const uint32_t *lut = nullptr)
 {
-    const LanePixel lp = lane_pixel(views, nviews, tile, log2_bw);
+    const LanePixel lp = lane_pixel<true>(views, nviews, tile, log2_bw);
     const ViewDev &v = views[lp.view];
     if (lp.col >= v.ncol || lp.row >= v.nrow) return;
     const int64_t pix = v.pix_off + (int64_t)lp.row * v.ncol + lp.col;
