@@ -94,6 +94,38 @@ static void p_defaults(const tomo_geometry *g, int64_t npix, const GridDev &gd, 
     }
 }
 
+// P's walk through the x-fastest cube, from MI355X times of single calls (us;
+// the machine loop / the compiler's loop with updates under the mask / by
+// selects).  The machine loop takes 15 VALU instructions a step against 23, but
+// its axis updates under the mask are one dependent chain, and four of a lane's
+// gathers in flight evict lines that its next voxels in x would still find.
+// - One to four wavefronts a SIMD (52000 to 260000 lines of sight), no denser
+//   than voxels, many of them along x: too few wavefronts to hide the chain.
+//   128^3 under 8 x 128^2: 70 / 66 / 63; 105x161x146 under 8 x 131x107: 74 / 72 /
+//   69; 170^3 under 5 x 150^2: 116 / 112 / 107; 200x100x120 under 16 x 90x80: 88 /
+//   73 / 70; 203x215x138 under 48 x 58x39: 173 / 130 / 126; 200x190x180 under 2 x
+//   200^2, lines 0.87 along x: 90 / 82 / 78.  Not where they run across x, whose
+//   gathers use whole lines (the same, none along x: 26 / 38 / 42; 300^3 under
+//   one view of 256^2, a quarter along x: 58 / 71 / 78), with one or two views
+//   in between (300^3, half: 109 / 112 / 116), with lines closer together
+//   (160x170x150 under one view of 300x200, 1.6 to a voxel: 18 to 30 / 20 to 31 /
+//   19 to 33; 227x186x214 under 4 x 256x173, 1.0 to a voxel: 206 / 238 / 216)
+//   or in cubes below 2^18 voxels (49x44x47 under 20 x 50x39: 11.9 / 12.3 / 12.6).
+// - Else lines further apart than voxels in a cube beyond an XCD's L2, which
+//   lose their lines: 200^3 under 4 x 60^2: 76 / 69 / 70; 256^3 under 8 x 64^2: 83 /
+//   80 / 82; 183x265x329 under 4 x 93x86: 64 / 61 / 60.
+static XWalk p_walk_default(const tomo_geometry *g, int64_t npix, const GridDev &gd, double rays_per_voxel)
+{
+    double along[3] = {0.0, 0.0, 0.0};  // planes of each axis the views' central lines cross
+    for (int k = 0; k < g->nviews; ++k)
+        for (int a = 0; a < 3; ++a) along[a] += fabs(g->views[k].w[a]) / gd.delta[a];
+    const double x_share = along[0] / (along[0] + along[1] + along[2]);
+    if (npix > 52000 && npix <= 260000 && gd.nvox >= ((int64_t)1 << 18) &&
+        rays_per_voxel < (npix <= 150000 ? 1.1 : 0.95) && x_share >= (g->nviews > 2 ? 0.35 : 0.8))
+        return XWalk::few;
+    return gd.nvox >= ((int64_t)1 << 20) && rays_per_voxel < 0.7 ? XWalk::two : XWalk::four;
+}
+
 int set_error(int status, const char *fmt, ...)
 {
     char buf[512];
@@ -299,14 +331,7 @@ static int build_plan(const tomo_geometry *g, int64_t npix, Plan &p)
         p.bp_pitch = med < 2.3 ? 0 : (med < 3.3 ? 1 : (med < 6.0 ? 2 : 3));
         const double side = std::min(gd.delta[0], std::min(gd.delta[1], gd.delta[2]));
         p_defaults(g, npix, gd, med * side / vox, p.p_auto);
-        // Lines of sight further apart than voxels in a cube beyond an XCD's L2:
-        // the x-fastest walk is bound by the lines its gathers bring in, and with
-        // four of a lane's gathers in flight fewer of them are still there for
-        // the lane's next voxel in x (200x100x120 under 16 x 90x80: 74 us with
-        // two, 88 with four; 180x157x103 under 11 x 100x83: 99 and 104;
-        // 105x161x146 under 8 x 131x107: 75 and 76; 260^3 under 27 x 90x65: 305
-        // and 297).
-        p.p_sparse = gd.nvox >= ((int64_t)1 << 20) && med * side / vox < 0.7;
+        p.p_walk = p_walk_default(g, npix, gd, med * side / vox);
     }
     hipError_t e = hipMalloc((void **)&p.views_d, sizeof(ViewDev) * hv.size());
     if (e != hipSuccess) return set_error(TOMO_ENOMEM, "view table allocation: %s", hipGetErrorString(e));

@@ -44,6 +44,13 @@ struct GridDev {
     int32_t pad;
 };
 
+// P's walk through the x-fastest cube (Plan::p_walk).
+enum class XWalk : int32_t {
+    four,  // the machine loop, four gathers in flight per lane
+    two,   // the compiler's, axes updated under the mask, two in flight
+    few,   // the same with axes updated by selects
+};
+
 // Wave-level ray bundle inside a 16x16 tile: each 64-lane wavefront takes a
 // bw x bh block of pixels (bw * bh == 64), and the four wavefronts tile the
 // 16x16 workgroup tile; or (log2_bw == 0) each wavefront takes every other
@@ -51,7 +58,6 @@ struct GridDev {
 struct Bundle {
     int32_t log2_bw;    // 3 -> 8x8, 4 -> 16x4, 2 -> 4x16, 0 -> interleaved
     int32_t xcd_remap;  // tile order (xcd_order): 0 launch order, 1 a run per XCD, 2 runs per XCD in step
-    int32_t sparse = 0; // P's x-fastest walk keeps two gathers in flight instead of four
 };
 
 // Owner-computes P^T launch shape (device copy).
@@ -171,7 +177,7 @@ struct Plan {
     int32_t bp_pitch = 0;              // blocked P^T: log2 of the pixels between neighbouring lanes
     bool bp_rows = false;              // blocked P^T walks footprint row intervals (pixels finer than voxels)
     uint64_t size_class = 0;           // key of the autotuner's cache (size_class_of)
-    bool p_sparse = false;             // P's x-fastest walk keeps two gathers in flight
+    XWalk p_walk = XWalk::four;        // P's walk through the x-fastest cube
     int32_t p_auto[3] = {2, 1, 0};     // P's bundle, tile order and cube layout where the tuning leaves them open
     Plan() = default;
     Plan(const Plan &) = delete;

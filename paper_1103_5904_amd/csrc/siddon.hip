@@ -36,7 +36,7 @@ namespace tomo {
 
 // ------------------------------------------------------------- kernels
 
-template <bool kMapMask, bool kDataMask, bool kObstacle>
+template <bool kMapMask, bool kDataMask, bool kObstacle, XWalk kWalk>
 __global__ __launch_bounds__(kThreads) void k_project(
     GridDev g, const ViewDev *__restrict__ views, int32_t nviews, Bundle bun, int32_t maxit,
     const float *__restrict__ cube, const uint8_t *__restrict__ map_mask,
@@ -44,8 +44,8 @@ __global__ __launch_bounds__(kThreads) void k_project(
     const int *__restrict__ done_flag)
 {
     if (done_flag && *done_flag) return;
-    project_tile<kMapMask, kDataMask, kObstacle>(g, views, nviews, bun.log2_bw, block_tile(bun), maxit, cube,
-                                                 map_mask, data_mask, images, bun.sparse != 0);
+    project_tile<kMapMask, kDataMask, kObstacle, kWalk>(g, views, nviews, bun.log2_bw, block_tile(bun), maxit, cube,
+                                                        map_mask, data_mask, images);
 }
 
 template <bool kMapMask, bool kDataMask>
@@ -223,12 +223,20 @@ int launch_fill(float *x, int64_t n, float v, hipStream_t s)
 int launch_project_tuned(const Plan &p, const tomo_geometry *g, const float *cube, float *images,
                          bool use_map_mask, hipStream_t s, const int *done_flag, const tomo_tuning &tu)
 {
-    const Bundle b{tu.p_bundle, tu.p_xcd_remap, p.p_sparse ? 1 : 0};
+    const Bundle b{tu.p_bundle, tu.p_xcd_remap};
     const bool mm = use_map_mask && g->map_mask, dm = g->data_mask != nullptr;
+    // byte offsets of four and few end at 2^29 voxels
+    const XWalk walk = p.grid.nvox < ((int64_t)1 << 29) ? p.p_walk : XWalk::two;
     const dim3 grid((unsigned)p.ntiles), blk(kThreads);
-#define TOMO_LAUNCH_P3(M, D, O)                                                                     \
-    hipLaunchKernelGGL((k_project<M, D, O>), grid, blk, 0, s, p.grid, p.views_d, p.nviews, b,        \
+#define TOMO_LAUNCH_P4(M, D, O, W)                                                                  \
+    hipLaunchKernelGGL((k_project<M, D, O, W>), grid, blk, 0, s, p.grid, p.views_d, p.nviews, b,     \
                        p.max_steps, cube, g->map_mask, g->data_mask, images, done_flag)
+#define TOMO_LAUNCH_P3(M, D, O)                                                                     \
+    do {                                                                                            \
+        if (M || walk == XWalk::two) TOMO_LAUNCH_P4(M, D, O, XWalk::two);                           \
+        else if (walk == XWalk::few) TOMO_LAUNCH_P4(false, D, O, XWalk::few);                       \
+        else TOMO_LAUNCH_P4(false, D, O, XWalk::four);                                              \
+    } while (0)
 #define TOMO_LAUNCH_P(M, D)                                                                         \
     do {                                                                                            \
         if (p.grid.has_sph) TOMO_LAUNCH_P3(M, D, true);                                             \
@@ -240,6 +248,7 @@ int launch_project_tuned(const Plan &p, const tomo_geometry *g, const float *cub
     else TOMO_LAUNCH_P(false, false);
 #undef TOMO_LAUNCH_P
 #undef TOMO_LAUNCH_P3
+#undef TOMO_LAUNCH_P4
     return hip_fail(hipGetLastError(), "projection kernel launch");
 }
 

@@ -385,6 +385,45 @@ __device__ inline double ray_integrate(RayState &r, int maxit, Pos &pos, const S
     return a_last ? fma(da, value(xa), acc) : fma(db, value(xb), acc);
 }
 
+// 1.0 if t else 0.0: only the high word differs, so one select; fma(ds, f,
+// s) then equals s + ds or s exactly.
+__device__ inline double tie_factor(bool t)
+{
+    return __builtin_bit_cast(double, (uint64_t)(t ? 0x3FF00000u : 0u) << 32);
+}
+
+// Sum over the ray's segments of length x voxel value, in parameter units, for
+// launches of a few wavefronts a SIMD (Plan::p_few): the axes are updated by
+// selects, which do not depend on each other as updates under the mask do, and
+// two gathers are in flight per lane.  23 VALU instructions a step.
+template <class Load>
+__device__ inline double ray_integrate_few(RayState &r, int maxit, uint32_t pos, const uint32_t (&st)[3], Load &&load)
+{
+    double acc = 0.0, dl_prev = 0.0, scur = 0.0;
+    float x_prev = 0.0f;
+    auto step = [&]() {  // true once the ray has ended
+        const double m = fmin(fmin(r.s[0], r.s[1]), fmin(r.s[2], r.send));
+        const uint32_t o = pos;
+        const double dl = m - scur;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const bool t = (r.s[a] == m);
+            r.s[a] = fma(r.ds[a], tie_factor(t), r.s[a]);  // s + ds or s, exact on the common grid
+            pos += t ? st[a] : 0u;
+        }
+        scur = m;
+        const float x = load(o);
+        acc = fma(dl_prev, (double)x_prev, acc);
+        x_prev = x;
+        dl_prev = dl;
+        return m >= r.send;
+    };
+    for (int it = 0; it < maxit; it += 4) {
+        if (step() || step() || step() || step()) break;
+    }
+    return fma(dl_prev, (double)x_prev, acc);
+}
+
 // ---- the two hot walks of P as one machine loop each.  What the compiler
 // makes of ray_integrate keeps the four exits of a body apart with mask
 // arithmetic, register copies and a wait for the newest gather; here a step
@@ -400,6 +439,11 @@ __device__ inline double ray_integrate(RayState &r, int maxit, Pos &pos, const S
 // step and 0.76 ms from the x-fastest cube before), by L2 where they are as far
 // apart as voxels (256^3 under 64 x 256^2: 1.37 ms, 22 GB of lines from L2; 4.64
 // ms x-fastest).  One gather in flight less: 5% slower there, even elsewhere.
+// The loop starts 16 bytes past a 64-byte line: where a SIMD has one or two
+// wavefronts, the instruction fetch shows, and a start at a multiple of 32 bytes
+// is slower (x-fastest, offsets 0 / 8 / 16 / 24 / 32 / 48: 160x170x150 under one
+// view of 300x200 19.9 / 18.2 / 18.3 / 18.7 / 19.9 / 18.1 us; 92x103x82 under
+// 98x58 19.2 / 17.5 / 17.6 / 18.0 / 19.2 / 17.6).
 //
 // Axis A's update where its crossing is the event M.  TERM reads the axis'
 // offset term for the next step.
@@ -457,7 +501,8 @@ __device__ inline double ray_integrate(RayState &r, int maxit, Pos &pos, const S
 #define TOMO_WALK(MIN, LOAD, TERM, P0, P1, P2)                    \
     "s_mov_b64 %[en], exec\n\t"                                   \
     "s_mov_b64 %[sv], exec\n\t" TERM("0") TERM("1") TERM("2")     \
-    "\n.Ltomo_walk_%=:\n\t"                                       \
+    "\n\t.p2align 6\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n" \
+    ".Ltomo_walk_%=:\n\t"                                         \
     TOMO_STEP("0", "1", "ma", "mb", MIN, LOAD, TERM, P0, P1, P2)  \
     TOMO_STEP("1", "2", "mb", "ma", MIN, LOAD, TERM, P0, P1, P2)  \
     TOMO_STEP("2", "3", "ma", "mb", MIN, LOAD, TERM, P0, P1, P2)  \
@@ -567,12 +612,13 @@ __device__ inline int64_t block_tile(const Bundle &b)
 
 // P for one 16x16 tile (all threads of the workgroup): each lane's pixel =
 // sum over its ray's segments of length x voxel value, written to images.
-template <bool kMapMask, bool kDataMask, bool kObstacle>
+// kWalk: four and few address a frame below 2^29 voxels by byte offsets; two,
+// and the walk that tests the map mask, take every frame.
+template <bool kMapMask, bool kDataMask, bool kObstacle, XWalk kWalk>
 __device__ inline void project_tile(const GridDev &g, const ViewDev *__restrict__ views, int32_t nviews,
                                     int log2_bw, int64_t tile, int32_t maxit,
                                     const float *__restrict__ cube, const uint8_t *__restrict__ map_mask,
-                                    const uint8_t *__restrict__ data_mask, float *__restrict__ images,
-                                    bool sparse = false)
+                                    const uint8_t *__restrict__ data_mask, float *__restrict__ images)
 {
     const LanePixel lp = lane_pixel(views, nviews, tile, log2_bw);
     const ViewDev &v = views[lp.view];
@@ -582,40 +628,51 @@ __device__ inline void project_tile(const GridDev &g, const ViewDev *__restrict_
     RayState r;
     if ((!kDataMask || data_mask[pix]) && ray_setup<kObstacle>(g, v, lp.col, lp.row, r)) {
         const float *__restrict__ base = cube + (int64_t)v.frame * g.nvox;
-        // a buffer resource spans below 2^32 bytes: a frame of 2^30 voxels
-        // takes plain global loads, their offsets clamped into the frame as
-        // the buffer's range check would
-        const bool wide = g.nvox >= ((int64_t)1 << 30);
-        const uint32_t last = (uint32_t)(g.nvox - 1);
-        const auto rc = make_rsrc(base, wide ? 0u : (uint32_t)(g.nvox * 4));
         double acc;
-        // offsets in bytes where int32 holds them (and the machine loop walks)
-        const uint32_t unit = !kMapMask && !sparse && g.nvox < ((int64_t)1 << 29) ? 4u : 1u;
-        uint32_t pos = (uint32_t)r.off * unit;
-        const uint32_t st[3] = {(uint32_t)r.st[0] * unit, (uint32_t)r.st[1] * unit, (uint32_t)r.st[2] * unit};
-        const auto plain = [](float x) { return (double)x; };
-        if constexpr (kMapMask) {
-            const auto rm = make_rsrc(map_mask, (uint32_t)g.nvox);
-            struct Masked {
-                float x;
-                uint32_t keep;
-            };
-            const auto kept = [](const Masked &t) { return t.keep ? (double)t.x : 0.0; };
-            if (wide)
-                acc = ray_integrate<kObstacle>(
-                    r, maxit, pos, st, [&](uint32_t o) { return Masked{base[min(o, last)], buf_load_u8(rm, o)}; }, kept);
-            else
-                acc = ray_integrate<kObstacle>(
-                    r, maxit, pos, st, [&](uint32_t o) { return Masked{buf_load_f32(rc, o * 4u), buf_load_u8(rm, o)}; },
-                    kept);
-        } else if (wide) {
-            acc = ray_integrate<kObstacle>(r, maxit, pos, st, [&](uint32_t o) { return base[min(o, last)]; }, plain);
-        } else if (unit == 4u) {
-            uint32_t p3[3] = {pos, 0u, 0u};
-            acc = ray_integrate_buffer<kObstacle, false>(r, maxit, p3, st, rsrc_words(base, (uint32_t)(g.nvox * 4)));
+        if constexpr (!kMapMask && kWalk != XWalk::two) {
+            const uint32_t st[3] = {(uint32_t)r.st[0] * 4u, (uint32_t)r.st[1] * 4u, (uint32_t)r.st[2] * 4u};
+            if constexpr (kWalk == XWalk::few) {
+                const auto rc = make_rsrc(base, (uint32_t)(g.nvox * 4));
+                acc = ray_integrate_few(r, maxit, (uint32_t)r.off * 4u, st,
+                                        [&](uint32_t o) { return buf_load_f32(rc, o); });
+            } else {
+                uint32_t pos[3] = {(uint32_t)r.off * 4u, 0u, 0u};
+                acc = ray_integrate_buffer<kObstacle, false>(r, maxit, pos, st,
+                                                             rsrc_words(base, (uint32_t)(g.nvox * 4)));
+            }
         } else {
-            acc = ray_integrate<kObstacle>(r, maxit, pos, st, [&](uint32_t o) { return buf_load_f32(rc, o * 4u); },
-                                           plain);
+            // a buffer resource spans below 2^32 bytes: a frame of 2^30 voxels
+            // takes plain global loads, their offsets clamped into the frame as
+            // the buffer's range check would
+            const bool wide = g.nvox >= ((int64_t)1 << 30);
+            const uint32_t last = (uint32_t)(g.nvox - 1);
+            const auto rc = make_rsrc(base, wide ? 0u : (uint32_t)(g.nvox * 4));
+            uint32_t pos = (uint32_t)r.off;
+            const uint32_t st[3] = {(uint32_t)r.st[0], (uint32_t)r.st[1], (uint32_t)r.st[2]};
+            if constexpr (kMapMask) {
+                const auto rm = make_rsrc(map_mask, (uint32_t)g.nvox);
+                struct Masked {
+                    float x;
+                    uint32_t keep;
+                };
+                const auto kept = [](const Masked &t) { return t.keep ? (double)t.x : 0.0; };
+                if (wide)
+                    acc = ray_integrate<kObstacle>(
+                        r, maxit, pos, st, [&](uint32_t o) { return Masked{base[min(o, last)], buf_load_u8(rm, o)}; },
+                        kept);
+                else
+                    acc = ray_integrate<kObstacle>(
+                        r, maxit, pos, st,
+                        [&](uint32_t o) { return Masked{buf_load_f32(rc, o * 4u), buf_load_u8(rm, o)}; }, kept);
+            } else {
+                const auto plain = [](float x) { return (double)x; };
+                if (wide)
+                    acc = ray_integrate<kObstacle>(r, maxit, pos, st, [&](uint32_t o) { return base[min(o, last)]; },
+                                                   plain);
+                else
+                    acc = ray_integrate<kObstacle>(r, maxit, pos, st,
+                                                   [&](uint32_t o) { return buf_load_f32(rc, o * 4u); }, plain);
+            }
         }
         out = (float)(acc * (r.dn * v.gain));
     }
