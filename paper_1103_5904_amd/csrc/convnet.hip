@@ -1120,9 +1120,12 @@ struct GradFactors {
 
 // This thread's share of output o of layer kLayer's gradient, pair by pair in
 // FP64: voxels outside the volume have no part, nor (layer 2) have zeros of f.
+// A wavefront takes runs of eight rows, so that sixteen loads are under way; a
+// NaN in one thread's share is the result (*stop), and the others end.
 template <int kLayer>
-__device__ inline double grad_by_pairs(int o, const GradFactors &p, const Vol &d)
+__device__ inline double grad_by_pairs(int o, const GradFactors &p, const Vol &d, volatile int *stop)
 {
+    constexpr int kRun = 8;
     const int nw = (kLayer == 2 ? kC : 1) * kC * kTaps;
     const bool bias = o >= nw;
     const int q = bias ? 0 : o / kTaps, t = bias ? 13 : o % kTaps;  // 13: the voxel itself
@@ -1131,20 +1134,33 @@ __device__ inline double grad_by_pairs(int o, const GradFactors &p, const Vol &d
     const int ox = t % 3 - 1, oy = (t / 3) % 3 - 1, oz = t / 9 - 1;
     const int rows = d.ny * d.nz;
     double acc = 0.0;
-    for (int row = threadIdx.x >> 6; row < rows; row += kThreads / 64) {
-        const int jj = row % d.ny + oy, kk = row / d.ny + oz;
-        if (jj < 0 || jj >= d.ny || kk < 0 || kk >= d.nz) continue;
-        const int64_t vr = (int64_t)row * d.nx, hr = ((int64_t)kk * d.ny + jj) * d.nx + ox;
-        for (int i = threadIdx.x & 63; i < d.nx; i += 64) {
-            if (i + ox < 0 || i + ox >= d.nx) continue;
-            const float f = kLayer == 3 ? p.ff[vr + i] : bf2f(p.fb[(vr + i) * kC + cf]);
-            if (bias) {
-                acc += (double)f;
-            } else if (!(kLayer == 2 && f == 0.0f)) {
-                const float h = kLayer == 1 ? p.hf[hr + i] : bf2f(p.hb[(hr + i) * kC + ch]);
-                acc += (double)f * (double)h;
+    for (int row0 = (threadIdx.x >> 6) * kRun; row0 < rows && !*stop; row0 += kThreads / 64 * kRun) {
+        int64_t h0[kRun];  // voxel (0, row) shifted by the tap's rows (-1: no pair)
+        int j = row0 % d.ny, k = row0 / d.ny;
+#pragma unroll
+        for (int u = 0; u < kRun; ++u) {
+            const int jj = j + oy, kk = k + oz;
+            const bool in = row0 + u < rows && jj >= 0 && jj < d.ny && kk >= 0 && kk < d.nz;
+            h0[u] = in ? ((int64_t)kk * d.ny + jj) * d.nx : -1;
+            if (++j == d.ny) {
+                j = 0;
+                ++k;
             }
         }
+        for (int i = threadIdx.x & 63; i < d.nx; i += 64) {
+            if (i + ox < 0 || i + ox >= d.nx) continue;
+            float f[kRun], h[kRun];
+#pragma unroll
+            for (int u = 0; u < kRun; ++u) {
+                const int64_t v = h0[u] < 0 ? 0 : (int64_t)(row0 + u) * d.nx + i, w = h0[u] < 0 ? 0 : h0[u] + i + ox;
+                f[u] = kLayer == 3 ? p.ff[v] : bf2f(p.fb[v * kC + cf]);
+                h[u] = bias ? 1.0f : (kLayer == 1 ? p.hf[w] : bf2f(p.hb[w * kC + ch]));
+            }
+#pragma unroll
+            for (int u = 0; u < kRun; ++u)
+                if (h0[u] >= 0 && !(kLayer == 2 && f[u] == 0.0f)) acc += (double)f[u] * (double)h[u];
+        }
+        if (acc != acc) *stop = 1;
     }
     return acc;
 }
@@ -1179,9 +1195,12 @@ __global__ __launch_bounds__(kThreads) void k_reduce_parts(const double *__restr
     const bool again = k == 0 && o < width && !isfinite(s);
     if (!__syncthreads_or(again ? 1 : 0)) return;
     __shared__ double lds[4];
+    __shared__ int stop;
     for (int q = 0; q < kRedOut && blockIdx.x * kRedOut + q < width; ++q) {
         if (isfinite(red[0][q])) continue;
-        const double sum = block_sum(grad_by_pairs<kLayer>(blockIdx.x * kRedOut + q, factors, d), lds);
+        if (threadIdx.x == 0) stop = 0;
+        __syncthreads();
+        const double sum = block_sum(grad_by_pairs<kLayer>(blockIdx.x * kRedOut + q, factors, d, &stop), lds);
         if (threadIdx.x == 0) grad[off + blockIdx.x * kRedOut + q] = (float)sum;
     }
 }
