@@ -405,9 +405,7 @@ __device__ inline void march_place(const March &m, const Vol &d, int item, int &
     z1 = min(z0 + m.cz, d.nz);
 }
 
-constexpr int kZX = 16, kZY = 16, kZR = kZX + 2;  // a column's outputs; rows and columns of its input plane
-constexpr int kZPlane = kZR * (kZY + 2);          // input voxels of a plane
-constexpr int kZLoads = (2 * kZPlane + kThreads - 1) / kThreads;
+constexpr int kZX = 16, kZY = 16, kZR = kZX + 2;  // a column's outputs; columns of its input plane
 static_assert(kZY == 4 * (kThreads / 64), "four rows per wavefront");
 
 // Largest activation the marching 16 -> 16 kernel addresses through one buffer
@@ -427,6 +425,7 @@ constexpr int64_t kMaxMarchVoxels = ((int64_t)1 << 27) - 1;
 // the three workgroups of a CU overlap in part (35.9 and 32.4 before the reads
 // were issued one group of products ahead; a whole plane ahead costs the
 // third workgroup its registers and wins nothing).
+// kWaves: four wavefronts on 16 rows, or two on 8 (half_columns).
 // kMode: what the products become.
 //   kForward: out = ReLU(bias + conv);
 //   kMasked: out = conv where mask > 0, else 0 (the data gradient through the
@@ -440,19 +439,21 @@ struct LastOut {
     const double *norm2;
     const uint8_t *map_mask;
 };
-template <int kMode>
-__global__ __launch_bounds__(kThreads) void k_conv16z(const uint16_t *__restrict__ in,
+template <int kMode, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void k_conv16z(const uint16_t *__restrict__ in,
                                                       const bf16x8 *__restrict__ frag,
                                                       const float *__restrict__ bias, Vol d, March m,
                                                       const uint16_t *__restrict__ mask,
                                                       uint16_t *__restrict__ out, LastOut last,
                                                       const int *__restrict__ skip)
 {
+    constexpr int kRows = 4 * kWaves, kZPlane = kZR * (kRows + 2);  // output rows; input voxels of a plane
+    constexpr int kZLoads = (2 * kZPlane + kWaves * 64 - 1) / (kWaves * 64);
     __shared__ uint4 buf[4][2 * kZPlane];
     if (skip && *skip) return;
     int cx, cy, z0, z1;
     march_place(m, d, march_first(), cx, cy, z0, z1);
-    const int x0 = cx * kZX, y0 = cy * kZY;
+    const int x0 = cx * kZX, y0 = cy * kRows;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const auto rs = make_rsrc(in, (uint32_t)(d.n * kC * 2));
     const uint32_t plane_bytes = (uint32_t)(d.nx * d.ny) * (kC * 2);
@@ -461,7 +462,7 @@ __global__ __launch_bounds__(kThreads) void k_conv16z(const uint16_t *__restrict
     uint32_t poff[kZLoads];
 #pragma unroll
     for (int u = 0; u < kZLoads; ++u) {
-        const int sl = (u * (kThreads / 64) + wave) * 64 + lane;
+        const int sl = (u * kWaves + wave) * 64 + lane;
         const int h = sl >= kZPlane ? 1 : 0, rv = sl - h * kZPlane;
         const int gx = x0 + rv % kZR - 1, gy = y0 + rv / kZR - 1;
         const bool ok = sl < 2 * kZPlane && gx >= 0 && gx < d.nx && gy >= 0 && gy < d.ny;
@@ -472,7 +473,7 @@ __global__ __launch_bounds__(kThreads) void k_conv16z(const uint16_t *__restrict
         const uint32_t zo = zin ? (uint32_t)z * plane_bytes : 0u;
 #pragma unroll
         for (int u = 0; u < kZLoads; ++u) {
-            const int c = u * (kThreads / 64) + wave;
+            const int c = u * kWaves + wave;
             if (c * 64 + lane < 2 * kZPlane) {
                 const uint32_t off = zin && poff[u] != kOut ? poff[u] + zo : kOut;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -576,24 +577,26 @@ __global__ __launch_bounds__(kThreads) void k_conv16z(const uint16_t *__restrict
 // positions, and the loop body holds four planes.
 // 128^3: 21.7 us (29.8 with one 16 x 4 x 4 tile per workgroup, each tap's input
 // split where it was read); writing a1 alone takes about 10 us.
-constexpr int kZ1Loads = (kZPlane + kThreads - 1) / kThreads;
-__global__ __launch_bounds__(kThreads) void k_conv1z(const bf16x8 *__restrict__ frag1, const float *__restrict__ P,
+template <int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void k_conv1z(const bf16x8 *__restrict__ frag1, const float *__restrict__ P,
                                                      const float *__restrict__ x, Vol d, March m,
                                                      const double *__restrict__ norm2, uint16_t *__restrict__ a1,
                                                      const int *__restrict__ skip)
 {
+    constexpr int kLanes = kWaves * 64, kRows = 4 * kWaves, kZPlane = kZR * (kRows + 2);
+    constexpr int kZ1Loads = (kZPlane + kLanes - 1) / kLanes;
     __shared__ uint32_t xs[4][kZPlane];
     if (skip && *skip) return;
     int cx, cy, z0, z1;
     march_place(m, d, march_first(), cx, cy, z0, z1);
     const float s = read_scale(norm2);
     const float inv = s > 0.0f ? 1.0f / s : 0.0f;
-    const int x0 = cx * kZX, y0 = cy * kZY;
+    const int x0 = cx * kZX, y0 = cy * kRows;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int64_t poff[kZ1Loads];  // in-plane offset of this thread's staged voxels (-1: outside)
 #pragma unroll
     for (int u = 0; u < kZ1Loads; ++u) {
-        const int e = u * kThreads + threadIdx.x;
+        const int e = u * kLanes + threadIdx.x;
         const int gx = x0 + e % kZR - 1, gy = y0 + e / kZR - 1;
         poff[u] = e < kZPlane && gx >= 0 && gx < d.nx && gy >= 0 && gy < d.ny ? (int64_t)gy * d.nx + gx : -1;
     }
@@ -609,7 +612,7 @@ __global__ __launch_bounds__(kThreads) void k_conv1z(const bf16x8 *__restrict__ 
 #pragma clang fp contract(off)  // the remainder is that of the rounded product
 #pragma unroll
         for (int u = 0; u < kZ1Loads; ++u) {
-            const int e = u * kThreads + threadIdx.x;
+            const int e = u * kLanes + threadIdx.x;
             const float t = v[u] * inv;
             const uint16_t h = f2bf(t);
             if (e < kZPlane) xs[slot][e] = (uint32_t)h << 16 | f2bf(t - bf2f(h));
@@ -1312,42 +1315,70 @@ static unsigned march_grid(const void *kernel, const Vol &d, int cx, int cy, Mar
     return (unsigned)(most > 0 && m.items > most ? most : m.items);
 }
 
+// Columns of 8 rows instead of 16, two wavefronts each, where a workgroup has
+// one plane, there are more of them than CUs and 8-row columns hold at least a
+// tenth fewer rows past the volume's edge: 33^3 18.6 -> 17.5 us, 100x33x17 20.9
+// -> 19.1, 25x40x60 19.0 -> 17.9 (forward).  More columns read more rim: 48^3,
+// whose rows fill 16, 19.3 and 20.0; up to one per CU they add waits: 17x33x50
+// 16.4 and 17.6.
+static bool half_columns(const Vol &d)
+{
+    const int64_t items = (int64_t)((d.nx + kZX - 1) / kZX) * ((d.ny + kZY - 1) / kZY) * d.nz;
+    return items > 256 && items <= 768 && 10 * ((d.ny + 7) / 8 * 8) <= 9 * ((d.ny + kZY - 1) / kZY * kZY);
+}
+
+template <int kMode, int kWaves>
+static void launch_conv16z(const uint16_t *in, const bf16x8 *frag, const float *bias, const Vol &d,
+                           const uint16_t *mask, uint16_t *out, const LastOut &last, const int *skip, hipStream_t s)
+{
+    March m;
+    const unsigned nb = march_grid(reinterpret_cast<const void *>(k_conv16z<kMode, kWaves>), d, kZX, 4 * kWaves, m, 0,
+                                   kWaves * 64);
+    hipLaunchKernelGGL((k_conv16z<kMode, kWaves>), dim3(nb), dim3(kWaves * 64), 0, s, in, frag, bias, d, m, mask, out,
+                       last, skip);
+}
+
 // The layers on a stored activation: the marching kernels, or one tile per
 // workgroup where an activation passes the marching kernel's reach.
 template <int kMode>
 static void launch_conv16(const uint16_t *in, const bf16x8 *frag, const float *bias, const Vol &d,
                           const uint16_t *mask, uint16_t *out, const int *skip, hipStream_t s)
 {
-    if (d.n <= kMaxMarchVoxels) {
-        March m;
-        const unsigned nb = march_grid(reinterpret_cast<const void *>(k_conv16z<kMode>), d, kZX, kZY, m);
-        hipLaunchKernelGGL(k_conv16z<kMode>, dim3(nb), dim3(kThreads), 0, s, in, frag, bias, d, m, mask, out,
-                           LastOut{}, skip);
-    } else {
+    if (d.n > kMaxMarchVoxels)
         hipLaunchKernelGGL(k_conv16, tile_grid(d), dim3(kThreads), 0, s, in, frag, bias, d, kMode == kForward ? 1 : 0,
                            mask, out, skip);
-    }
+    else if (half_columns(d))
+        launch_conv16z<kMode, 2>(in, frag, bias, d, mask, out, LastOut{}, skip, s);
+    else
+        launch_conv16z<kMode, 4>(in, frag, bias, d, mask, out, LastOut{}, skip, s);
+}
+
+template <int kWaves>
+static void launch_conv1z(const bf16x8 *frag1, const float *P, const float *x, const Vol &d, const double *norm2,
+                          uint16_t *a1, const int *skip, hipStream_t s)
+{
+    March m;
+    const unsigned nb = march_grid(reinterpret_cast<const void *>(k_conv1z<kWaves>), d, kZX, 4 * kWaves, m, 0, kWaves * 64);
+    hipLaunchKernelGGL(k_conv1z<kWaves>, dim3(nb), dim3(kWaves * 64), 0, s, frag1, P, x, d, m, norm2, a1, skip);
 }
 
 static void launch_conv1(const bf16x8 *frag1, const float *P, const float *x, const Vol &d, const double *norm2,
                          uint16_t *a1, const int *skip, hipStream_t s)
 {
-    March m;
-    const unsigned nb = march_grid(reinterpret_cast<const void *>(k_conv1z), d, kZX, kZY, m);
-    hipLaunchKernelGGL(k_conv1z, dim3(nb), dim3(kThreads), 0, s, frag1, P, x, d, m, norm2, a1, skip);
+    if (half_columns(d)) launch_conv1z<2>(frag1, P, x, d, norm2, a1, skip, s);
+    else launch_conv1z<4>(frag1, P, x, d, norm2, a1, skip, s);
 }
 
 static void launch_conv3(const bf16x8 *frag3, const float *P, const uint16_t *a2, const Vol &d, const double *norm2,
                          const uint8_t *map_mask, float *out, const int *skip, hipStream_t s)
 {
-    if (d.n <= kMaxMarchVoxels) {
-        March m;
-        const unsigned nb = march_grid(reinterpret_cast<const void *>(k_conv16z<kLast>), d, kZX, kZY, m);
-        hipLaunchKernelGGL(k_conv16z<kLast>, dim3(nb), dim3(kThreads), 0, s, a2, frag3, P + OB3, d, m,
-                           (const uint16_t *)nullptr, (uint16_t *)nullptr, LastOut{out, norm2, map_mask}, skip);
-    } else {
+    const LastOut last{out, norm2, map_mask};
+    if (d.n > kMaxMarchVoxels)
         hipLaunchKernelGGL(k_conv3, tile_grid(d), dim3(kThreads), 0, s, frag3, P, a2, d, norm2, map_mask, out, skip);
-    }
+    else if (half_columns(d))
+        launch_conv16z<kLast, 2>(a2, frag3, P + OB3, d, nullptr, nullptr, last, skip, s);
+    else
+        launch_conv16z<kLast, 4>(a2, frag3, P + OB3, d, nullptr, nullptr, last, skip, s);
 }
 
 // z = s N(x / s) on the device (s = sqrt(*norm2), or 1), zero where the map
