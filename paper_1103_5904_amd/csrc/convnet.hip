@@ -1320,7 +1320,8 @@ static unsigned march_grid(const void *kernel, const Vol &d, int cx, int cy, Mar
 // tenth fewer rows past the volume's edge: 33^3 18.6 -> 17.5 us, 100x33x17 20.9
 // -> 19.1, 25x40x60 19.0 -> 17.9 (forward).  More columns read more rim: 48^3,
 // whose rows fill 16, 19.3 and 20.0; up to one per CU they add waits: 17x33x50
-// 16.4 and 17.6.
+// 16.4 and 17.6.  A training pass keeps 16 rows, nearer to its gradients' columns
+// (20x50x50 68 us, 70 with 8).
 static bool half_columns(const Vol &d)
 {
     const int64_t items = (int64_t)((d.nx + kZX - 1) / kZX) * ((d.ny + kZY - 1) / kZY) * d.nz;
@@ -1342,12 +1343,12 @@ static void launch_conv16z(const uint16_t *in, const bf16x8 *frag, const float *
 // workgroup where an activation passes the marching kernel's reach.
 template <int kMode>
 static void launch_conv16(const uint16_t *in, const bf16x8 *frag, const float *bias, const Vol &d,
-                          const uint16_t *mask, uint16_t *out, const int *skip, hipStream_t s)
+                          const uint16_t *mask, uint16_t *out, bool half, const int *skip, hipStream_t s)
 {
     if (d.n > kMaxMarchVoxels)
         hipLaunchKernelGGL(k_conv16, tile_grid(d), dim3(kThreads), 0, s, in, frag, bias, d, kMode == kForward ? 1 : 0,
                            mask, out, skip);
-    else if (half_columns(d))
+    else if (half)
         launch_conv16z<kMode, 2>(in, frag, bias, d, mask, out, LastOut{}, skip, s);
     else
         launch_conv16z<kMode, 4>(in, frag, bias, d, mask, out, LastOut{}, skip, s);
@@ -1363,19 +1364,19 @@ static void launch_conv1z(const bf16x8 *frag1, const float *P, const float *x, c
 }
 
 static void launch_conv1(const bf16x8 *frag1, const float *P, const float *x, const Vol &d, const double *norm2,
-                         uint16_t *a1, const int *skip, hipStream_t s)
+                         uint16_t *a1, bool half, const int *skip, hipStream_t s)
 {
-    if (half_columns(d)) launch_conv1z<2>(frag1, P, x, d, norm2, a1, skip, s);
+    if (half) launch_conv1z<2>(frag1, P, x, d, norm2, a1, skip, s);
     else launch_conv1z<4>(frag1, P, x, d, norm2, a1, skip, s);
 }
 
 static void launch_conv3(const bf16x8 *frag3, const float *P, const uint16_t *a2, const Vol &d, const double *norm2,
-                         const uint8_t *map_mask, float *out, const int *skip, hipStream_t s)
+                         const uint8_t *map_mask, float *out, bool half, const int *skip, hipStream_t s)
 {
     const LastOut last{out, norm2, map_mask};
     if (d.n > kMaxMarchVoxels)
         hipLaunchKernelGGL(k_conv3, tile_grid(d), dim3(kThreads), 0, s, frag3, P, a2, d, norm2, map_mask, out, skip);
-    else if (half_columns(d))
+    else if (half)
         launch_conv16z<kLast, 2>(a2, frag3, P + OB3, d, nullptr, nullptr, last, skip, s);
     else
         launch_conv16z<kLast, 4>(a2, frag3, P + OB3, d, nullptr, nullptr, last, skip, s);
@@ -1395,9 +1396,10 @@ int convnet_forward_dev(const tomo_cube &c, const float *P, const float *x, floa
     bf16x8 *frag = (bf16x8 *)(base + 2 * align256(sizeof(uint16_t) * kC * d.n));
     if (prep_frags)
         hipLaunchKernelGGL(k_conv_frags, dim3((kFragFwd + 255) / 256), dim3(256), 0, s, P, 0, frag);
-    launch_conv1(frag + kFrag1, P, x, d, norm2, a1, skip, s);
-    launch_conv16<kForward>(a1, frag, P + OB2, d, nullptr, a2, skip, s);
-    launch_conv3(frag + kFrag3, P, a2, d, norm2, map_mask, out, skip, s);
+    const bool half = half_columns(d);
+    launch_conv1(frag + kFrag1, P, x, d, norm2, a1, half, skip, s);
+    launch_conv16<kForward>(a1, frag, P + OB2, d, nullptr, a2, half, skip, s);
+    launch_conv3(frag + kFrag3, P, a2, d, norm2, map_mask, out, half, skip, s);
     return hip_fail(hipGetLastError(), "convnet forward launch");
 }
 
@@ -1451,10 +1453,10 @@ static int convnet_train_pass(const tomo_cube *cube, const float *params_d, cons
     hipLaunchKernelGGL(k_conv_frags, dim3((kFragFwd + 255) / 256), dim3(256), 0, s, params_d, 0, w.frag);
     hipLaunchKernelGGL(k_conv_frags, dim3((kFragConv + 255) / 256), dim3(256), 0, s, params_d, 1, w.fragT);
     const int *noskip = nullptr;
-    launch_conv1(w.frag + kFrag1, params_d, x_d, d, nullptr, w.a1, noskip, s);
-    launch_conv16<kForward>(w.a1, w.frag, params_d + OB2, d, nullptr, w.a2, noskip, s);
+    launch_conv1(w.frag + kFrag1, params_d, x_d, d, nullptr, w.a1, false, noskip, s);
+    launch_conv16<kForward>(w.a1, w.frag, params_d + OB2, d, nullptr, w.a2, false, noskip, s);
     if (target_d) {
-        launch_conv3(w.frag + kFrag3, params_d, w.a2, d, nullptr, nullptr, w.out, noskip, s);
+        launch_conv3(w.frag + kFrag3, params_d, w.a2, d, nullptr, nullptr, w.out, false, noskip, s);
         // loss and d loss / d out
         hipLaunchKernelGGL(k_mse, dim3(kLossBlocks), dim3(kThreads), 0, s, w.out, target_d, n, w.g,
                            w.loss_part);
@@ -1477,7 +1479,7 @@ static int convnet_train_pass(const tomo_cube *cube, const float *params_d, cons
     hipLaunchKernelGGL(k_wgrad2, dim3(nb), dim3(kWThreads), 0, s, w.gh, w.a1, d, m, w.part);
     reduce(std::integral_constant<int, 2>{}, nb, kWPart, OW2, GradFactors{w.gh, w.a1, nullptr, nullptr});
     // d loss / d h1 = [a1 > 0] conv^T(gh); written over a2 (no longer needed)
-    launch_conv16<kMasked>(w.gh, w.fragT, nullptr, d, w.a1, w.a2, noskip, s);
+    launch_conv16<kMasked>(w.gh, w.fragT, nullptr, d, w.a1, w.a2, false, noskip, s);
     // layer 1
     nb = march_grid(reinterpret_cast<const void *>(k_wgrad_field<true>), d, kZX, kZY, m, kFieldBlocks);
     hipLaunchKernelGGL(k_wgrad_field<true>, dim3(nb), dim3(kThreads), 0, s, w.a2, x_d, d, m, w.part);
