@@ -216,13 +216,13 @@ int tomo_trace_ray(const tomo_geometry *g, int32_t view, int32_t col,
  *     walks inside a 16x16 workgroup tile: 2 = 4x16, 3 = 8x8, 4 = 16x4 pixels,
  *     0 = the 64 lanes interleaved at a 2-pixel pitch over the whole tile
  *     (p_bundle: P; bp_bundle: the binned and atomic back-projections; the
- *     blocked one walks each footprint 256 pixels at a time in row-major
+ *     blocked one walks each footprint in runs of 64 pixels in row-major
  *     order and takes no bundle shape).
  *   p_xcd_remap, bp_xcd_remap: order of the tiles (of the voxel-block items
  *     for the blocked back-projection) over the 8 XCDs: 0 = launch order,
- *     1 = one contiguous run per XCD, 2 = runs of 32 (P from the caller's
- *     x-fastest array: 64) per XCD with all XCDs advancing through the list
- *     together (a multi-frame cube then keeps one frame in the caches at a
+ *     1 = one contiguous run per XCD, 2 = runs of 64 (P from bricks and the
+ *     blocked back-projection: 32) per XCD with all XCDs advancing through
+ *     the list together (a multi-frame cube then keeps one frame in the caches at a
  *     time).
  *   bp_lds_bins: 64-bit LDS bins per workgroup of the binned
  *     back-projection (512..8192, i.e. 4..64 KiB; larger boxes mean fewer

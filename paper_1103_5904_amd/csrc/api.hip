@@ -72,13 +72,16 @@ tomo_tuning settle_p(const Plan &p, tomo_tuning t, bool single)
 //   lines share the x-fastest lines well (193x150x77 under 20 x 512^2: 0.449
 //   against 0.458; 120x110x100 under 28 x 512^2: 0.419 against 0.457), unless
 //   rows of a multiple of 128 bytes put a plane's rows on the same cache sets
-//   (128^3 under 28 x 512^2: 0.73 -> 0.51; 160^3 under 20 x 1024^2: 2.00 -> 1.54);
+//   (128^3 under 28 x 512^2: 0.73 -> 0.51; 160^3 under 20 x 1024^2: 2.00 -> 1.54;
+//   96x121x99 under 28 x 400^2: 0.385 -> 0.275; 160x110x70 under 30 x 600x500:
+//   0.671 -> 0.640);
 // - sparser than 0.7 voxels: lines of sight share no lines, and a line that is
 //   flat in z and long in x serves the longest run of one ray: bricks of 8^3
 //   and 16x4 bundles.  512^3 under 64 x 256^2: 13.2 -> 6.9 ms (4^3: 11.4); 256^3
 //   under 64 x 128^2: 1.32 -> 0.79 (4^3: 1.03).  At 0.8 the two are even.
 // Fewer crossings than the copy is worth: 320x280x300 under 60 x 60^2 (3.6 per
-// voxel) 0.48 ms x-fastest, 0.52 from bricks.
+// voxel) 0.48 ms x-fastest, 0.52 from bricks.  Solves and batches, which keep the
+// copy's place but copy per P, take the same lines.
 static void p_defaults(const tomo_geometry *g, int64_t npix, const GridDev &gd, double rays_per_voxel, int32_t (&out)[3])
 {
     const double steps = 0.5 * (double)npix * ((double)gd.n[0] + gd.n[1] + gd.n[2]);

@@ -125,8 +125,9 @@ __device__ inline int64_t xcd_remap_chunked(int64_t b, int64_t nb)
 // Tile order of a launch: 0 = launch order, 1 = one contiguous run per
 // XCD, 2 = runs of kRun per XCD advancing together.  Walks from bricks and the
 // blocked P^T take runs of 32 (Thomson pB of a 256^3 frame under 60 x 512^2,
-// bricks: 1904 us, 2267 with runs of 64), walks of the x-fastest cube 64
-// (105x161x146 under 8 x 131x107: 65 us, 77 with 32).
+// bricks: 1904 us, 2267 with runs of 64; the blocked P^T of that geometry 4117,
+// 4148 with 64, of smaller ones even), walks of the x-fastest cube 64 (105x161x146
+// under 8 x 131x107: 65 us, 77 with 32).
 template <int64_t kRun = 32>
 __device__ inline int64_t xcd_order(int32_t mode, int64_t b, int64_t nb)
 {

@@ -326,10 +326,10 @@ __device__ inline double next_event(const double (&s)[3], double send)
 }
 
 // Walk the ray voxel by voxel.  visit(off, dl) receives the flat voxel
-// offset and the parameter length of the segment (length = dl * |d|).  Simultaneous crossings advance every tied
-// axis in one step.  maxit bounds the loop whatever the arithmetic does; the
-// loop body holds four steps, so the bound is tested once per four (it may
-// run up to three steps past it).
+// offset and the parameter length of the segment (length = dl * |d|).
+// Simultaneous crossings advance every tied axis in one step.  maxit bounds
+// the loop whatever the arithmetic does; the loop body holds four steps, so
+// the bound is tested once per four (it may run up to three steps past it).
 template <class Visit>
 __device__ inline void ray_walk(RayState &r, int maxit, Visit &&visit)
 {
@@ -393,7 +393,7 @@ __device__ inline double tie_factor(bool t)
 }
 
 // Sum over the ray's segments of length x voxel value, in parameter units, for
-// launches of a few wavefronts a SIMD (Plan::p_few): the axes are updated by
+// launches of a few wavefronts a SIMD (XWalk::few): the axes are updated by
 // selects, which do not depend on each other as updates under the mask do, and
 // two gathers are in flight per lane.  23 VALU instructions a step.
 template <class Load>
